@@ -217,3 +217,11 @@ def test_fused_backward_adam_matches_separate_calls(n, deg, window):
             total += x.size
         print(f"step {t}: {same}/{total} values bit-identical")
     assert np.isfinite(fu.loss_value())
+
+
+# Whole blocks (and a last block of 4) move their SH spans as 16-byte vectors
+# also where a row (3 or 27 floats) is not a whole number of them; a last
+# block of 1 takes the element-wise path beside them.
+@pytest.mark.parametrize("n,deg", [(512, 0), (512, 2), (1284, 2), (1281, 3)])
+def test_fused_backward_adam_vector_spans(n, deg):
+    test_fused_backward_adam_matches_separate_calls(n, deg, synth.WINDOW_PAPER)
