@@ -225,3 +225,11 @@ def test_fused_backward_adam_matches_separate_calls(n, deg, window):
 @pytest.mark.parametrize("n,deg", [(512, 0), (512, 2), (1284, 2), (1281, 3)])
 def test_fused_backward_adam_vector_spans(n, deg):
     test_fused_backward_adam_matches_separate_calls(n, deg, synth.WINDOW_PAPER)
+
+
+# The tile heights the image loss picks by image size: 16 rows once that gives
+# 512 workgroups (449x401, 321x299) and for images much narrower than a tile
+# (16x200, 7x65), 8 below (63x9); each with ragged edges.
+@pytest.mark.parametrize("W,H", [(449, 401), (321, 299), (16, 200), (7, 65), (63, 9)])
+def test_image_loss_tile_heights(W, H):
+    test_image_loss(W, H, 0.2)
