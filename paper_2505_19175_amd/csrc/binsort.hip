@@ -4,16 +4,14 @@
 // tile front to back by the depth key, ties by triangle index.  Sorting the
 // 64-bit (tile, depth) keys of all M instances would take 6 radix passes over
 // M.  Instead the instances are first grouped by tile, then each tile's run
-// is put in depth order.  Grouping, when the tile counters fit in LDS (up to
-// kGroupTiles tiles) and the huge tiles are not sorted segment-wise:
-//   1'. G groups of consecutive triangles count their instances per tile in
-//       LDS (a G x tiles matrix), a column scan gives each group its offset
-//       inside each tile, one workgroup scans the tile totals into the ranges
-//       and the longest-first tile order, and the groups place every instance
-//       at tile start + group offset + an LDS cursor (four launches, no pass
-//       over the instance list)
-// Otherwise (more tiles, or the segmented sort of huge tiles, which needs the
-// runs in index order):
+// is put in depth order.  Grouping, when the huge tiles are not sorted
+// segment-wise:
+//   1'. groups of consecutive triangles count their instances per tile in LDS
+//       and, once the column sums are known, place every instance at tile
+//       start + group offset + an LDS cursor: no pass over the instance list
+//       (one to four launches, by size: "grouping by group tile counts" below)
+// Otherwise (the segmented sort of huge tiles, which needs the runs in index
+// order, and single views of more than 12288 tiles):
 //   1. count the tiles of every triangle, in index order, and scan the counts
 //   2. emit one instance per (triangle, tile) in index order
 //   3. stable LSD radix sort of the instances by tile id,
@@ -493,13 +491,23 @@ __device__ void order_tiles(int n, Len len_of, uint32_t* __restrict__ order,
         s_huge = 0u;
     }
     __syncthreads();
-    auto key = [&](int t) {
-        return (kLenBuckets - 1) - (int)min(len_of(t), (uint32_t)(kLenBuckets - 1));
+    // Atomics of one address take a wave's lanes one by one, so the counters
+    // that most lanes would hit (the empty tiles' bucket, the long and huge
+    // counts) get one add per wave.
+    auto key = [&](uint32_t L) {
+        return (kLenBuckets - 1) - (int)min(L, (uint32_t)(kLenBuckets - 1));
     };
     for (int t = tid; t < n; t += kOrderThreads) {
-        atomicAdd(&h[key(t)], 1u);
-        if (len_of(t) > (uint32_t)kWaveSortMax) atomicAdd(&s_long, 1u);
-        if (len_of(t) > (uint32_t)kHugeLen) atomicAdd(&s_huge, 1u);
+        const uint32_t L = len_of(t);
+        const uint64_t act = __ballot(1), empty = __ballot(L == 0u);
+        const uint64_t lng = __ballot(L > (uint32_t)kWaveSortMax);
+        const uint64_t huge = __ballot(L > (uint32_t)kHugeLen);
+        if (L != 0u) atomicAdd(&h[key(L)], 1u);
+        if (lane == (int)__builtin_ctzll(act)) {
+            if (empty) atomicAdd(&h[kLenBuckets - 1], (uint32_t)__popcll(empty));
+            if (lng) atomicAdd(&s_long, (uint32_t)__popcll(lng));
+            if (huge) atomicAdd(&s_huge, (uint32_t)__popcll(huge));
+        }
     }
     __syncthreads();
     if (n_long && tid == 0) n_long[0] = s_long;
@@ -520,7 +528,20 @@ __device__ void order_tiles(int n, Len len_of, uint32_t* __restrict__ order,
     h[2 * tid] = pre;
     h[2 * tid + 1] = pre + a0;
     __syncthreads();
-    for (int t = tid; t < n; t += kOrderThreads) order[atomicAdd(&h[key(t)], 1u)] = (uint32_t)t;
+    for (int t = tid; t < n; t += kOrderThreads) {
+        const uint32_t L = len_of(t);
+        const uint64_t empty = __ballot(L == 0u);
+        uint32_t at = 0u;
+        if (L != 0u) {
+            at = atomicAdd(&h[key(L)], 1u);
+        } else {
+            const int lead = (int)__builtin_ctzll(empty);
+            if (lane == lead) at = atomicAdd(&h[kLenBuckets - 1], (uint32_t)__popcll(empty));
+            at = (uint32_t)__shfl((int)at, lead, 64) +
+                 (uint32_t)__popcll(empty & ((1ull << lane) - 1ull));
+        }
+        order[at] = (uint32_t)t;
+    }
 }
 
 __global__ __launch_bounds__(kOrderThreads) void k_tile_order(
@@ -555,103 +576,129 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tfi
 }
 
 // ---------------------------------------------------------------------------
-// 1'. grouping by group tile counts (up to kGroupTiles tiles)
+// 1'. grouping by group tile counts
 // ---------------------------------------------------------------------------
-// When the tile counters fit in LDS, steps 1-3 become four launches with no
-// pass over the instance list: G groups of consecutive entries count their
-// instances per tile in LDS (G x tiles matrix), a column scan turns the matrix
-// into each group's offset inside each tile, one workgroup scans the tile
-// totals into the ranges and the longest-first order, and the groups walk
-// their entries again and place every instance at its tile's start + the
-// group's offset + an LDS cursor.  Inside a tile the instances are then in
+// When the tile counters fit in LDS, steps 1-3 need no pass over the instance
+// list: G groups of consecutive entries count their instances per tile in LDS
+// (G x tiles matrix), a column scan turns the matrix into each group's offset
+// inside each tile, and the groups walk their entries again and place every
+// instance at its tile's start + the group's offset + an LDS cursor.  The
+// starts are the scan of the tile totals, which every placing workgroup
+// repeats in LDS (tiles / 1024 values a thread) instead of waiting for a
+// launch of its own; one more workgroup of that launch writes the ranges and
+// the longest-first order meanwhile.  Inside a tile the instances are then in
 // group order but not in index order inside a group; the per-tile sort orders
 // by the unique (depth, index) key anyway (the workgroup sort of the huge
 // tiles sorts by index first).
+//
+// The launches, by size (all bound by the latency of their dependent phases):
+//   one group (up to kOneEntries entries): one workgroup does it all
+//   a small matrix (up to kFoldCells counts): count, place -- the placing
+//     workgroups sum the matrix columns themselves
+//   else: count, column scan, place
+//   more than kGroupTiles tiles (a batch's budget): count, column scan, starts
+//     and ranges by one workgroup, place, each for kWideTiles of the batch's
+//     own tiles at a time (counts of 16 bits, cursors of 32)
+// Against four launches for every size up to kGroupTiles tiles and the radix
+// chain's eleven beyond, measured for the binning before the per-tile sort:
+//   1k triangles, 64 tiles      23.7 -> 7.2 us
+//   20k, 256 tiles              27.0 -> 11.6 us
+//   300k, 3600 tiles            31.6 -> 21.5 us
+//   3M, 3600 tiles              52.2 -> 47 us
+//   batch of 1 view of 1M, 920 tiles      57 -> 25 us
+//   batch of 4 views of 1M, 13600 tiles   92 -> 75 us
 constexpr int kGroupThreads = 1024;
 constexpr int kMaxGroups = 256;
-constexpr int kGroupEntries = 4096;   // fewest entries per group
-constexpr int kGroupTiles = 12288;    // tile counters in LDS (48 KB)
-
-constexpr int kGroupRun = 8;   // consecutive entries a thread loads at once
+constexpr int kGroupEntries = 1024;   // fewest entries per group
+constexpr int kOneEntries = 4096;     // entries one workgroup bins alone
+constexpr int64_t kFoldCells = 1 << 16;
+constexpr int kGroupTiles = 12288;    // 32-bit tile counters in LDS (48 KB)
+constexpr int kWideTiles = 16384;     // tiles of a window: 16-bit counters 32 KB, cursors 64 KB
+constexpr int64_t kWideEntries = 65528;   // most entries of a group: no 16-bit count overflows
 
 // The group a workgroup takes.  Workgroups are dealt to the eight XCDs in
 // turn, so consecutive groups go to one XCD: they write neighbouring slots of
 // every tile, and fewer cache lines are written in part by several XCDs'
 // caches.
 constexpr int kXcds = 8;
-__device__ __forceinline__ int xcd_group(int G)
+__device__ __forceinline__ int xcd_group(int b, int G)
 {
-    const int b = blockIdx.x;
     return (G % kXcds) == 0 ? (b % kXcds) * (G / kXcds) + b / kXcds : b;
 }
 
-// Entries [e0, e1) of group g: ceil(n / G), rounded up to whole runs.
+// Part g of G of n entries: ceil(n / G) each, rounded up to whole runs of 8.
 __device__ __forceinline__ void group_span(int64_t n, int G, int g, int64_t& e0, int64_t& e1)
 {
     int64_t per = (n + G - 1) / G;
-    per = (per + kGroupRun - 1) / kGroupRun * kGroupRun;
+    per = (per + 7) / 8 * 8;
     e0 = min(n, (int64_t)g * per);
     e1 = min(n, e0 + per);
 }
 
-// Tile counts and rectangles (x0, x1, y0, y1 as two words) of entries
-// e .. e + kGroupRun - 1; counts at or past e1 read as zero.  Whole aligned
-// runs use 16-byte loads, all issued before any is used.
+// A run: the R consecutive entries a thread takes at once, their tile counts
+// and rectangles (x0, x1, y0, y1 as two words); counts at or past the end read
+// as zero.  Runs of eight read their counts with 16-byte loads, then the
+// rectangles of the visible entries only, all issued before any is used; runs
+// of one, for groups of few entries per thread, read both at once.
+template <int R>
+struct Run {
+    uint32_t n[R];
+    uint2 rb[R];
+};
+
+template <int R>
 __device__ __forceinline__ void load_run(const uint32_t* __restrict__ ntiles,
                                          const uint2* __restrict__ rect, int64_t e, int64_t e1,
-                                         uint32_t (&n)[kGroupRun], uint2 (&rb)[kGroupRun])
+                                         Run<R>& u)
 {
-    if (e + kGroupRun <= e1 && (reinterpret_cast<uintptr_t>(ntiles + e) & 15u) == 0u &&
-        (reinterpret_cast<uintptr_t>(rect + e) & 15u) == 0u) {
-        const uint4* pn = reinterpret_cast<const uint4*>(ntiles + e);
-        const uint4* pr = reinterpret_cast<const uint4*>(rect + e);
-        uint4 a[2], b[kGroupRun / 2];
-#pragma unroll
-        for (int r = 0; r < 2; ++r) a[r] = pn[r];
-#pragma unroll
-        for (int r = 0; r < kGroupRun / 2; ++r) b[r] = pr[r];
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            n[4 * r + 0] = a[r].x;
-            n[4 * r + 1] = a[r].y;
-            n[4 * r + 2] = a[r].z;
-            n[4 * r + 3] = a[r].w;
-        }
-#pragma unroll
-        for (int r = 0; r < kGroupRun / 2; ++r) {
-            rb[2 * r] = make_uint2(b[r].x, b[r].y);
-            rb[2 * r + 1] = make_uint2(b[r].z, b[r].w);
-        }
+    static_assert(R == 1 || R == 8, "runs of one or eight");
+    if constexpr (R == 1) {
+        const bool ok = e < e1;
+        u.n[0] = ok ? ntiles[e] : 0u;
+        u.rb[0] = ok ? rect[e] : make_uint2(0u, 0u);
     } else {
+        if (e + 8 <= e1 && (reinterpret_cast<uintptr_t>(ntiles + e) & 15u) == 0u) {
+            const uint4* pn = reinterpret_cast<const uint4*>(ntiles + e);
+            const uint4 a = pn[0], b = pn[1];
+            u.n[0] = a.x; u.n[1] = a.y; u.n[2] = a.z; u.n[3] = a.w;
+            u.n[4] = b.x; u.n[5] = b.y; u.n[6] = b.z; u.n[7] = b.w;
+        } else {
 #pragma unroll
-        for (int r = 0; r < kGroupRun; ++r) {
-            n[r] = e + r < e1 ? ntiles[e + r] : 0u;
-            rb[r] = n[r] != 0u ? rect[e + r] : make_uint2(0u, 0u);
+            for (int r = 0; r < 8; ++r) u.n[r] = e + r < e1 ? ntiles[e + r] : 0u;
         }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) u.rb[r] = u.n[r] != 0u ? rect[e + r] : make_uint2(0u, 0u);
     }
 }
 
-// The first tile of entry e's rectangle, the rectangle's width in tiles and
-// the tile row pitch.
+// The entries the binning takes: N of them (or *d_n), of one view; or of the
+// views of a batch, entry e being triangle e % per_view of view e / per_view.
+struct TileGrid {
+    const ts_view* views;   // null: one view, pitch tiles_x
+    int64_t per_view;
+    int tiles_x;
+    int64_t N;
+    const uint32_t* d_n;
+};
+
+// The tiles of one view: offset of the first one and row pitch.
+struct ViewTiles {
+    uint32_t off;
+    int pitch;
+};
+
+// The first tile of an entry's rectangle, the rectangle's width in tiles and
+// the tile row pitch (a visible entry's rectangle has no negative side).
 struct TileWalk {
     uint32_t first;
     int nx, tw;
 };
 
-__device__ __forceinline__ TileWalk tile_walk(uint32_t e, uint2 rb, int tiles_x,
-                                              const ts_view* __restrict__ views, int64_t per_view)
+__device__ __forceinline__ TileWalk tile_walk(uint2 rb, const ViewTiles& vt)
 {
-    const int x0 = (int16_t)(rb.x & 0xffffu), x1 = (int16_t)(rb.x >> 16);
-    const int y0 = (int16_t)(rb.y & 0xffffu);
-    const int tx0 = x0 / kTile, nx = x1 / kTile - tx0 + 1, ty0 = y0 / kTile;
-    uint32_t toff = 0;
-    int tw = tiles_x;
-    if (views) {   // batched: entry = view * per_view + triangle
-        const ts_view& V = views[e / (uint64_t)per_view];
-        toff = V.tile_offset;
-        tw = (int)V.tiles_x;
-    }
-    return {toff + (uint32_t)(ty0 * tw + tx0), nx, tw};
+    static_assert(kTile == 16, "tile of a pixel by shifts");
+    const uint32_t tx0 = (rb.x & 0xffffu) >> 4, tx1 = rb.x >> 20, ty0 = (rb.y & 0xffffu) >> 4;
+    return {vt.off + ty0 * (uint32_t)vt.pitch + tx0, (int)(tx1 - tx0 + 1u), vt.pitch};
 }
 
 // Calls f(tile) for the n tiles of a rectangle, row by row.
@@ -669,24 +716,20 @@ __device__ __forceinline__ void for_tiles(const TileWalk& tw, uint32_t n, F f)
     }
 }
 
-// Calls f(tile, entry) for every instance of the run's entries e .. e + 7:
+// Calls f(tile, entry) for every instance of the run's entries e .. e + R - 1:
 // entries of up to kLaneTiles tiles by their own lane, larger ones (a
 // triangle can cover hundreds of tiles) one at a time by all active lanes of
 // the wave, so no lane walks a long rectangle alone.
 constexpr uint32_t kLaneTiles = 8;
 
-template <class F>
-__device__ __forceinline__ void for_run_tiles(int64_t e, const uint32_t (&n)[kGroupRun],
-                                              const uint2 (&rb)[kGroupRun], int tiles_x,
-                                              const ts_view* __restrict__ views, int64_t per_view,
-                                              F f)
+template <int R, class F>
+__device__ __forceinline__ void for_run_tiles(int64_t e, const Run<R>& u, const ViewTiles& vt, F f)
 {
 #pragma unroll
-    for (int r = 0; r < kGroupRun; ++r) {
-        if (n[r] != 0u && n[r] <= kLaneTiles) {
+    for (int r = 0; r < R; ++r) {
+        if (u.n[r] != 0u && u.n[r] <= kLaneTiles) {
             const uint32_t id = (uint32_t)(e + r);
-            for_tiles(tile_walk(id, rb[r], tiles_x, views, per_view), n[r],
-                      [&](uint32_t t) { f(t, id); });
+            for_tiles(tile_walk(u.rb[r], vt), u.n[r], [&](uint32_t t) { f(t, id); });
         }
     }
     const uint64_t act = __ballot(1);
@@ -694,16 +737,16 @@ __device__ __forceinline__ void for_run_tiles(int64_t e, const uint32_t (&n)[kGr
     const int lane = threadIdx.x & 63;
     const uint32_t rank = (uint32_t)__popcll(act & ((1ull << lane) - 1ull));
 #pragma unroll
-    for (int r = 0; r < kGroupRun; ++r) {
-        uint64_t want = __ballot(n[r] > kLaneTiles);
+    for (int r = 0; r < R; ++r) {
+        uint64_t want = __ballot(u.n[r] > kLaneTiles);
         while (want != 0ull) {   // the same for all active lanes
             const int src = (int)__builtin_ctzll(want);
             want &= want - 1ull;
-            const uint32_t ns = (uint32_t)__shfl((int)n[r], src, 64);
+            const uint32_t ns = (uint32_t)__shfl((int)u.n[r], src, 64);
             const uint32_t id = (uint32_t)__shfl((int)(uint32_t)(e + r), src, 64);
-            const uint2 rs = make_uint2((uint32_t)__shfl((int)rb[r].x, src, 64),
-                                        (uint32_t)__shfl((int)rb[r].y, src, 64));
-            const TileWalk tw = tile_walk(id, rs, tiles_x, views, per_view);
+            const uint2 rs = make_uint2((uint32_t)__shfl((int)u.rb[r].x, src, 64),
+                                        (uint32_t)__shfl((int)u.rb[r].y, src, 64));
+            const TileWalk tw = tile_walk(rs, vt);
             for (uint32_t k = rank; k < ns; k += nact) {
                 const uint32_t dy = k / (uint32_t)tw.nx, dx = k - dy * (uint32_t)tw.nx;
                 f(tw.first + dy * (uint32_t)tw.tw + dx, id);
@@ -712,52 +755,249 @@ __device__ __forceinline__ void for_run_tiles(int64_t e, const uint32_t (&n)[kGr
     }
 }
 
-// Per group: instances per tile (row g of hist, T wide), and the group's
-// instance and visible-entry totals in grp[g], grp[G + g].
-__global__ __launch_bounds__(kGroupThreads) void k_group_count(
-    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, int64_t N_host,
-    const uint32_t* __restrict__ d_n, int tiles_x, const ts_view* __restrict__ views,
-    int64_t per_view, int T, int G, uint32_t* __restrict__ hist, uint32_t* __restrict__ grp)
+// Calls f(tile, entry) for every instance of entries [e0, e1) of one view, runs
+// of R entries per thread; returns the number of this thread's visible
+// entries.
+template <int R, class F>
+__device__ __forceinline__ uint32_t for_span_tiles(int64_t e0, int64_t e1,
+                                                   const uint32_t* __restrict__ ntiles,
+                                                   const uint2* __restrict__ rect,
+                                                   const ViewTiles& vt, F f)
 {
-    extern __shared__ uint32_t s_h[];   // [T]
-    __shared__ uint32_t s_tmp[kGroupThreads / 64][2];
-    const int tid = threadIdx.x, g = xcd_group(G);
-    const int64_t N = d_n ? (int64_t)*d_n : N_host;
-    int64_t e0, e1;
-    group_span(N, G, g, e0, e1);
-    for (int t = tid; t < T; t += kGroupThreads) s_h[t] = 0u;
-    __syncthreads();
-    uint32_t m = 0, v = 0;
-    for (int64_t e = e0 + (int64_t)tid * kGroupRun; e < e1;
-         e += (int64_t)kGroupThreads * kGroupRun) {
-        uint32_t n[kGroupRun];
-        uint2 rb[kGroupRun];
-        load_run(ntiles, rect, e, e1, n, rb);
+    uint32_t vis = 0;
+    for (int64_t e = e0 + (int64_t)threadIdx.x * R; e < e1; e += (int64_t)kGroupThreads * R) {
+        Run<R> u;
+        load_run<R>(ntiles, rect, e, e1, u);
 #pragma unroll
-        for (int r = 0; r < kGroupRun; ++r) {
-            m += n[r];
-            v += n[r] != 0u ? 1u : 0u;
+        for (int r = 0; r < R; ++r) vis += u.n[r] != 0u ? 1u : 0u;
+        for_run_tiles<R>(e, u, vt, f);
+    }
+    return vis;
+}
+
+// The same for group g of G: a part of the one view's entries, or of one view
+// of a batch (G / views groups each, so a group's view is the workgroup's), or
+// some whole views where there are more views than groups.
+template <int R, class F>
+__device__ __forceinline__ uint32_t for_group_tiles(int G, int g,
+                                                    const uint32_t* __restrict__ ntiles,
+                                                    const uint2* __restrict__ rect,
+                                                    const TileGrid& tg, F f)
+{
+    const int64_t N = tg.d_n ? (int64_t)*tg.d_n : tg.N;
+    int64_t e0, e1;
+    if (!tg.views) {
+        group_span(N, G, g, e0, e1);
+        return for_span_tiles<R>(e0, e1, ntiles, rect, ViewTiles{0u, tg.tiles_x}, f);
+    }
+    const int nv = (int)((N + tg.per_view - 1) / tg.per_view);
+    const int gpv = nv > 0 ? max(1, G / nv) : 1;   // groups per view
+    uint32_t vis = 0;
+    for (int v = g / gpv; v < nv; v += (G + gpv - 1) / gpv) {
+        group_span(min(tg.per_view, N - v * tg.per_view), gpv, g % gpv, e0, e1);
+        const int64_t b = v * tg.per_view;
+        vis += for_span_tiles<R>(b + e0, b + e1, ntiles, rect,
+                                 ViewTiles{tg.views[v].tile_offset, (int)tg.views[v].tiles_x}, f);
+    }
+    return vis;
+}
+
+// Sum of one value per thread over the workgroup, in thread 0.
+__device__ __forceinline__ uint32_t group_sum(uint32_t v, uint32_t* s_tmp)
+{
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    if ((threadIdx.x & 63) == 0) s_tmp[threadIdx.x >> 6] = v;
+    __syncthreads();
+    uint32_t x = 0;
+    if (threadIdx.x == 0)
+        for (int j = 0; j < kGroupThreads / 64; ++j) x += s_tmp[j];
+    return x;
+}
+
+// Exclusive scan of s_t[0 .. T) in LDS by the workgroup, T <= kGroupTiles; each
+// thread owns a slice of consecutive tiles.  Returns the total.
+constexpr int kTileSlice = kGroupTiles / kGroupThreads;
+static_assert(kTileSlice * kGroupThreads == kGroupTiles, "whole slices");
+
+__device__ __forceinline__ uint64_t scan_tiles(uint32_t* s_t, int T, uint32_t* s_tmp)
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int per = (T + kGroupThreads - 1) / kGroupThreads, t0 = tid * per;
+    uint32_t s = 0;
+    for (int r = 0; r < per; ++r) s += t0 + r < T ? s_t[t0 + r] : 0u;
+    uint32_t inc = s;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += y;
+    }
+    if (lane == 63) s_tmp[w] = inc;
+    __syncthreads();
+    uint32_t start = inc - s;
+    uint64_t M = 0;
+    for (int j = 0; j < kGroupThreads / 64; ++j) {
+        start += j < w ? s_tmp[j] : 0u;
+        M += s_tmp[j];
+    }
+    for (int r = 0; r < per; ++r) {
+        if (t0 + r < T) {
+            const uint32_t c = s_t[t0 + r];
+            s_t[t0 + r] = start;
+            start += c;
         }
-        for_run_tiles(e, n, rb, tiles_x, views, per_view, [&](uint32_t t, uint32_t) {
-            if (t < (uint32_t)T) atomicAdd(&s_h[t], 1u);
+    }
+    __syncthreads();
+    return M;
+}
+
+// Where the binning writes what it found.
+struct GroupOut {
+    uint64_t capacity;
+    uint32_t* ranges;
+    uint32_t* order;
+    uint32_t* n_long;
+    uint32_t* n_huge;
+    uint32_t* d_M;
+    uint32_t* d_sortn;
+    uint32_t* d_ovf;
+    uint32_t* d_Nv;
+};
+
+__device__ __forceinline__ void write_totals(uint64_t M, const GroupOut& o)
+{
+    *o.d_M = (uint32_t)min(M, (uint64_t)0xffffffffu);
+    *o.d_sortn = (uint32_t)min(M, o.capacity);
+    *o.d_ovf = M > o.capacity ? 1u : 0u;
+}
+
+// From the starts s_t[0 .. T) and the total M: the ranges (clamped to the
+// capacity; an empty tile's range is (0, 0)) and the longest-first order of
+// the first n tiles.
+__device__ __forceinline__ void write_ranges(const uint32_t* s_t, int T, int n, uint64_t M,
+                                             const GroupOut& o, OrderSmem& sm)
+{
+    auto bounds = [&](int t) {
+        const uint64_t a = s_t[t], b = t + 1 < T ? (uint64_t)s_t[t + 1] : M;
+        return make_uint2((uint32_t)min(a, o.capacity), (uint32_t)min(b, o.capacity));
+    };
+    uint2* r2 = reinterpret_cast<uint2*>(o.ranges);
+    const bool pair = (reinterpret_cast<uintptr_t>(o.ranges) & 7u) == 0u;
+    for (int t = threadIdx.x; t < T; t += kGroupThreads) {
+        uint2 r = bounds(t);
+        if (r.x == r.y) r = make_uint2(0u, 0u);
+        if (pair) {
+            r2[t] = r;
+        } else {
+            o.ranges[2 * t] = r.x;
+            o.ranges[2 * t + 1] = r.y;
+        }
+    }
+    order_tiles(
+        n, [&](int t) { const uint2 r = bounds(t); return r.y - r.x; }, o.order, o.n_long,
+        o.n_huge, sm);
+}
+
+static_assert(kOrderThreads == kGroupThreads, "the order is made by a placing workgroup");
+
+// Puts an instance at slot p of the list, unless it is past the capacity (as
+// the clamped ranges say).
+__device__ __forceinline__ uint32_t cap32(uint64_t capacity)
+{
+    return capacity < 0xffffffffull ? (uint32_t)capacity : 0xffffffffu;
+}
+
+// One workgroup bins everything (N <= kOneEntries entries of one view, T <=
+// kGroupTiles).
+__global__ __launch_bounds__(kGroupThreads) void k_bin_one(
+    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T, const uint32_t* __restrict__ d_tiles,
+    GroupOut o, uint32_t* __restrict__ vals)
+{
+    extern __shared__ uint32_t s_t[];   // [T] counts, then starts, then cursors
+    __shared__ OrderSmem sm;
+    __shared__ uint32_t s_tmp[kGroupThreads / 64], s_tmp2[kGroupThreads / 64];
+    const int tid = threadIdx.x;
+    const int64_t N = tg.N;
+    const ViewTiles vt{0u, tg.tiles_x};
+    constexpr int kRounds = kOneEntries / kGroupThreads;
+    Run<1> u[kRounds];
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k)
+        load_run<1>(ntiles, rect, k * kGroupThreads + tid, N, u[k]);
+    for (int t = tid; t < T; t += kGroupThreads) s_t[t] = 0u;
+    __syncthreads();
+    uint32_t vis = 0;
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+        vis += u[k].n[0] != 0u ? 1u : 0u;
+        for_run_tiles<1>(k * kGroupThreads + tid, u[k], vt, [&](uint32_t t, uint32_t) {
+            if (t < (uint32_t)T) atomicAdd(&s_t[t], 1u);
         });
     }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        m += __shfl_xor(m, d, 64);
-        v += __shfl_xor(v, d, 64);
+    vis = group_sum(vis, s_tmp);   // a barrier inside: the counts are whole
+    const uint64_t M = scan_tiles(s_t, T, s_tmp2);
+    if (tid == 0) {
+        write_totals(M, o);
+        *o.d_Nv = vis;
     }
-    if ((tid & 63) == 0) {
-        s_tmp[tid >> 6][0] = m;
-        s_tmp[tid >> 6][1] = v;
-    }
+    write_ranges(s_t, T, d_tiles ? (int)min(*d_tiles, (uint32_t)T) : T, M, o, sm);
     __syncthreads();
+    const uint32_t cap = cap32(o.capacity);
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k)
+        for_run_tiles<1>(k * kGroupThreads + tid, u[k], vt, [&](uint32_t t, uint32_t id) {
+            if (t < (uint32_t)T) {
+                const uint32_t p = atomicAdd(&s_t[t], 1u);
+                if (p < cap) vals[p] = id;
+            }
+        });
+}
+
+// Tile counters of a group in LDS: 32 bits each, or 16 in the halves of a word
+// (WIDE).  bump returns the count before.
+template <bool WIDE>
+__device__ __forceinline__ uint32_t bump(uint32_t* s, uint32_t t)
+{
+    if constexpr (WIDE) {
+        const uint32_t sh = 16u * (t & 1u);
+        return (atomicAdd(&s[t >> 1], 1u << sh) >> sh) & 0xffffu;
+    } else {
+        return atomicAdd(&s[t], 1u);
+    }
+}
+
+// Per group: instances per tile (row g of hist, T wide) and the group's
+// visible entries in grp[g].  WIDE: only the batch's own tiles (*d_tiles of
+// the T budgeted) are counted, and the grid clears all ranges.
+template <int R, bool WIDE>
+__global__ __launch_bounds__(kGroupThreads) void k_group_count(
+    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T, const uint32_t* __restrict__ d_tiles,
+    int G, uint32_t* __restrict__ hist, uint32_t* __restrict__ grp, uint32_t* __restrict__ ranges)
+{
+    extern __shared__ uint32_t s_h[];   // [T] counters
+    __shared__ uint32_t s_tmp[kGroupThreads / 64];
+    const int tid = threadIdx.x, g = xcd_group(blockIdx.x, G);
+    const int Ta = WIDE && d_tiles ? (int)min(*d_tiles, (uint32_t)T) : T;
+    if constexpr (WIDE)
+        for (int64_t f = (int64_t)blockIdx.x * kGroupThreads + tid; f < 2 * (int64_t)T;
+             f += (int64_t)gridDim.x * kGroupThreads)
+            ranges[f] = 0u;
     uint32_t* row = hist + (int64_t)g * T;
-    for (int t = tid; t < T; t += kGroupThreads) row[t] = s_h[t];
-    if (tid < 2) {
-        uint32_t x = 0;
-        for (int j = 0; j < kGroupThreads / 64; ++j) x += s_tmp[j][tid];
-        grp[tid * G + g] = x;
+    for (int w0 = 0;; w0 += kWideTiles) {   // windows of tiles; one unless WIDE
+        const int m = WIDE ? min(kWideTiles, Ta - w0) : Ta;
+        const int words = WIDE ? (m + 1) / 2 : m;
+        for (int t = tid; t < words; t += kGroupThreads) s_h[t] = 0u;
+        __syncthreads();
+        uint32_t v = for_group_tiles<R>(G, g, ntiles, rect, tg, [&](uint32_t t, uint32_t) {
+            if constexpr (WIDE) t -= (uint32_t)w0;
+            if (t < (uint32_t)m) bump<WIDE>(s_h, t);
+        });
+        v = group_sum(v, s_tmp);   // a barrier inside: the counts are whole
+        if (tid == 0) grp[g] = v;
+        for (int t = tid; t < m; t += kGroupThreads)
+            row[w0 + t] = WIDE ? (s_h[t >> 1] >> (16 * (t & 1))) & 0xffffu : s_h[t];
+        if (!WIDE || w0 + kWideTiles >= Ta) return;
+        __syncthreads();
     }
 }
 
@@ -767,10 +1007,13 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_count(
 constexpr int kScanWaves = 16;
 constexpr int kScanSlice = kMaxGroups / kScanWaves;
 
-__global__ __launch_bounds__(64 * kScanWaves) void k_group_scan(uint32_t* __restrict__ hist, int T,
-                                                                int G, uint32_t* __restrict__ tot)
+__global__ __launch_bounds__(64 * kScanWaves) void k_group_scan(
+    uint32_t* __restrict__ hist, int T, const uint32_t* __restrict__ d_tiles, int G,
+    uint32_t* __restrict__ tot)
 {
     __shared__ uint32_t s_sum[kScanWaves][64];
+    const int Ta = d_tiles ? (int)min(*d_tiles, (uint32_t)T) : T;
+    if ((int)blockIdx.x * 64 >= Ta) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int t = blockIdx.x * 64 + lane;
     const int gq = (G + kScanWaves - 1) / kScanWaves, g0 = w * gq;
@@ -779,7 +1022,7 @@ __global__ __launch_bounds__(64 * kScanWaves) void k_group_scan(uint32_t* __rest
 #pragma unroll
     for (int j = 0; j < kScanSlice; ++j) {
         const int g = g0 + j;
-        x[j] = (j < gq && g < G && t < T) ? hist[(int64_t)g * T + t] : 0u;
+        x[j] = (j < gq && g < G && t < Ta) ? hist[(int64_t)g * T + t] : 0u;
         sum += x[j];
     }
     s_sum[w][lane] = sum;
@@ -794,112 +1037,155 @@ __global__ __launch_bounds__(64 * kScanWaves) void k_group_scan(uint32_t* __rest
 #pragma unroll
     for (int j = 0; j < kScanSlice; ++j) {
         const int g = g0 + j;
-        if (j < gq && g < G && t < T) {
+        if (j < gq && g < G && t < Ta) {
             hist[(int64_t)g * T + t] = run;
             run += x[j];
         }
     }
-    if (w == 0 && t < T) tot[t] = all;
+    if (w == 0 && t < Ta) tot[t] = all;
 }
 
-// One workgroup: the totals (M, min(M, capacity), overflow, N_v), the ranges
-// of the T tiles from the exclusive scan of their totals (clamped to the
-// capacity; an empty tile's range is (0, 0)), and the longest-first order of
-// the first n tiles.  tot[t] is replaced by the tile's unclamped start.
-constexpr int kRangeSlice = kGroupTiles / kOrderThreads;   // tiles per thread
-static_assert(kRangeSlice * kOrderThreads == kGroupTiles, "whole slices");
-static_assert(kMaxGroups <= kOrderThreads, "one group total per thread");
-
-__global__ __launch_bounds__(kOrderThreads) void k_group_ranges(
-    uint32_t* __restrict__ tot, int T, const uint32_t* __restrict__ d_tiles,
-    const uint32_t* __restrict__ grp, int G, uint64_t capacity, uint32_t* __restrict__ ranges,
-    uint32_t* __restrict__ order, uint32_t* __restrict__ n_long, uint32_t* __restrict__ n_huge,
-    uint32_t* __restrict__ d_M, uint32_t* __restrict__ d_sortn, uint32_t* __restrict__ d_ovf,
-    uint32_t* __restrict__ d_Nv)
+// The visible entries of all groups, in thread 0.
+__device__ __forceinline__ uint32_t sum_groups(const uint32_t* __restrict__ grp, int G,
+                                               uint32_t* s_tmp)
 {
-    extern __shared__ uint32_t s_len[];   // [T] clamped list lengths
-    __shared__ OrderSmem sm;
-    __shared__ uint32_t s_tmp[kOrderThreads / 64][2];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int t0 = tid * kRangeSlice;   // this thread's slice of tiles
-    uint32_t c[kRangeSlice];
-    uint32_t s = 0;
-#pragma unroll
-    for (int r = 0; r < kRangeSlice; ++r) {
-        c[r] = t0 + r < T ? tot[t0 + r] : 0u;
-        s += c[r];
-    }
-    uint32_t nv = tid < G ? grp[G + tid] : 0u;
-    uint32_t inc = s;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(inc, d, 64);
-        if (lane >= d) inc += y;
-        nv += __shfl_xor(nv, d, 64);
-    }
-    if (lane == 63) {
-        s_tmp[w][0] = inc;
-        s_tmp[w][1] = nv;
-    }
-    __syncthreads();
-    uint64_t start = inc - s, M = 0;
-    uint32_t NV = 0;
-    for (int j = 0; j < kOrderThreads / 64; ++j) {
-        start += j < w ? s_tmp[j][0] : 0u;
-        M += s_tmp[j][0];
-        NV += s_tmp[j][1];
-    }
-#pragma unroll
-    for (int r = 0; r < kRangeSlice; ++r) {
-        const int t = t0 + r;
-        if (t < T) {
-            const uint64_t end = start + c[r];
-            tot[t] = (uint32_t)start;
-            uint32_t a = (uint32_t)min(start, capacity), b = (uint32_t)min(end, capacity);
-            if (a == b) a = b = 0u;
-            ranges[2 * t] = a;
-            ranges[2 * t + 1] = b;
-            s_len[t] = b - a;
-            start = end;
-        }
-    }
-    if (tid == 0) {
-        *d_M = (uint32_t)M;
-        *d_sortn = (uint32_t)min(M, capacity);
-        *d_ovf = M > capacity ? 1u : 0u;
-        *d_Nv = NV;
-    }
-    __syncthreads();
-    const int n = d_tiles ? (int)min(*d_tiles, (uint32_t)T) : T;
-    order_tiles(n, [&](int t) { return s_len[t]; }, order, n_long, n_huge, sm);
+    static_assert(kMaxGroups <= kGroupThreads, "one group per thread");
+    return group_sum((int)threadIdx.x < G ? grp[threadIdx.x] : 0u, s_tmp);
 }
 
-// Per group: every instance goes to its tile's start + the group's offset in
-// the tile + the group's running count of the tile (LDS cursor); instances at
-// or past the capacity are dropped, as the clamped ranges say.
+// Workgroup 0 writes the ranges, the order and the totals; workgroup 1 + b
+// places the instances of a group.  FOLD: hist holds the raw counts, so each
+// workgroup sums the columns it needs; else the scanned offsets, with the
+// tile totals in tot.
+template <int R, bool FOLD>
 __global__ __launch_bounds__(kGroupThreads) void k_group_place(
-    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, int64_t N_host,
-    const uint32_t* __restrict__ d_n, int tiles_x, const ts_view* __restrict__ views,
-    int64_t per_view, int T, int G, const uint32_t* __restrict__ hist,
-    const uint32_t* __restrict__ start, uint64_t capacity, uint32_t* __restrict__ vals)
+    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T, const uint32_t* __restrict__ d_tiles,
+    int G, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ tot,
+    const uint32_t* __restrict__ grp, GroupOut o, uint32_t* __restrict__ vals)
 {
-    extern __shared__ uint32_t s_cur[];   // [T]
-    const int tid = threadIdx.x, g = xcd_group(G);
-    const uint32_t cap = capacity < 0xffffffffull ? (uint32_t)capacity : 0xffffffffu;
-    const int64_t N = d_n ? (int64_t)*d_n : N_host;
-    int64_t e0, e1;
-    group_span(N, G, g, e0, e1);
-    const uint32_t* row = hist + (int64_t)g * T;
-    for (int t = tid; t < T; t += kGroupThreads) s_cur[t] = start[t] + row[t];
+    extern __shared__ uint32_t s_t[];   // [T] totals, then starts, then cursors
+    __shared__ OrderSmem sm;
+    __shared__ uint32_t s_tmp[kGroupThreads / 64], s_tmp2[kGroupThreads / 64];
+    const int tid = threadIdx.x;
+    const bool head = blockIdx.x == 0;
+    const int g = head ? 0 : xcd_group((int)blockIdx.x - 1, G);
+    uint32_t before[kTileSlice];   // instances of tile tid + k * 1024 in groups before g
+#pragma unroll
+    for (int k = 0; k < kTileSlice; ++k) {
+        const int t = k * kGroupThreads + tid;
+        before[k] = 0u;
+        if (t >= T) continue;
+        uint32_t all = 0;
+        if constexpr (FOLD) {
+#pragma unroll 4
+            for (int j = 0; j < G; ++j) {
+                const uint32_t c = hist[(int64_t)j * T + t];
+                before[k] += j < g ? c : 0u;
+                all += c;
+            }
+        } else {
+            all = tot[t];
+            if (!head) before[k] = hist[(int64_t)g * T + t];
+        }
+        s_t[t] = all;
+    }
     __syncthreads();
-    for (int64_t e = e0 + (int64_t)tid * kGroupRun; e < e1;
-         e += (int64_t)kGroupThreads * kGroupRun) {
-        uint32_t n[kGroupRun];
-        uint2 rb[kGroupRun];
-        load_run(ntiles, rect, e, e1, n, rb);
-        for_run_tiles(e, n, rb, tiles_x, views, per_view, [&](uint32_t t, uint32_t id) {
-            if (t < (uint32_t)T) {
-                const uint32_t p = atomicAdd(&s_cur[t], 1u);
+    const uint64_t M = scan_tiles(s_t, T, s_tmp);
+    if (head) {
+        const uint32_t vis = sum_groups(grp, G, s_tmp2);
+        if (tid == 0) {
+            write_totals(M, o);
+            *o.d_Nv = vis;
+        }
+        write_ranges(s_t, T, d_tiles ? (int)min(*d_tiles, (uint32_t)T) : T, M, o, sm);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < kTileSlice; ++k) {
+        const int t = k * kGroupThreads + tid;
+        if (t < T) s_t[t] += before[k];
+    }
+    __syncthreads();
+    const uint32_t cap = cap32(o.capacity);
+    for_group_tiles<R>(G, g, ntiles, rect, tg, [&](uint32_t t, uint32_t id) {
+        if (t < (uint32_t)T) {
+            const uint32_t p = atomicAdd(&s_t[t], 1u);
+            if (p < cap) vals[p] = id;
+        }
+    });
+}
+
+// More tiles than a workgroup's 32-bit counters: one workgroup scans the
+// totals of the batch's tiles (*d_tiles of the T budgeted) in chunks into the
+// ranges, and writes the totals.  start[t] receives the unclamped starts.
+__global__ __launch_bounds__(kGroupThreads) void k_group_ranges_wide(
+    const uint32_t* __restrict__ tot, int T, const uint32_t* __restrict__ d_tiles,
+    const uint32_t* __restrict__ grp, int G, GroupOut o, uint32_t* __restrict__ start)
+{
+    constexpr int kPart = 8 * kGroupThreads;
+    __shared__ uint32_t s_t[kPart];
+    __shared__ uint32_t s_tmp[kGroupThreads / 64], s_tmp2[kGroupThreads / 64];
+    const int tid = threadIdx.x;
+    const int n = d_tiles ? (int)min(*d_tiles, (uint32_t)T) : T;
+    uint64_t M = 0;
+    for (int t0 = 0; t0 < n; t0 += kPart) {
+        const int m = min(kPart, n - t0);
+#pragma unroll
+        for (int k = 0; k < kPart / kGroupThreads; ++k) {
+            const int t = k * kGroupThreads + tid;
+            if (t < m) s_t[t] = tot[t0 + t];
+        }
+        __syncthreads();
+        const uint64_t sum = scan_tiles(s_t, m, s_tmp);
+        for (int t = tid; t < m; t += kGroupThreads) {
+            const uint64_t a = M + s_t[t], b = M + (t + 1 < m ? (uint64_t)s_t[t + 1] : sum);
+            const uint32_t ra = (uint32_t)min(a, o.capacity), rb = (uint32_t)min(b, o.capacity);
+            start[t0 + t] = (uint32_t)a;
+            if (ra != rb) {   // the counting launch cleared the ranges
+                o.ranges[2 * (t0 + t)] = ra;
+                o.ranges[2 * (t0 + t) + 1] = rb;
+            }
+        }
+        M += sum;
+        __syncthreads();   // the chunk is read by its neighbours' threads
+    }
+    const uint32_t vis = sum_groups(grp, G, s_tmp2);
+    if (tid == 0) {
+        write_totals(M, o);
+        *o.d_Nv = vis;
+    }
+}
+
+// Workgroup 0 makes the order from the ranges; workgroup 1 + b places a
+// group's instances, a window of tiles at a time.
+template <int R>
+__global__ __launch_bounds__(kGroupThreads) void k_group_place_wide(
+    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T, const uint32_t* __restrict__ d_tiles,
+    int G, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ start, GroupOut o,
+    uint32_t* __restrict__ vals)
+{
+    __shared__ uint32_t s_t[kWideTiles];   // cursors (64 KB)
+    static_assert(sizeof(OrderSmem) <= sizeof(s_t), "the order workgroup's tables");
+    const int tid = threadIdx.x;
+    const int Ta = d_tiles ? (int)min(*d_tiles, (uint32_t)T) : T;
+    if (blockIdx.x == 0) {
+        order_tiles(
+            Ta, [&](int t) { return o.ranges[2 * t + 1] - o.ranges[2 * t]; }, o.order, o.n_long,
+            o.n_huge, *reinterpret_cast<OrderSmem*>(s_t));
+        return;
+    }
+    const int g = xcd_group((int)blockIdx.x - 1, G);
+    const uint32_t* row = hist + (int64_t)g * T;
+    const uint32_t cap = cap32(o.capacity);
+    for (int w0 = 0; w0 < Ta; w0 += kWideTiles) {
+        const int m = min(kWideTiles, Ta - w0);
+        __syncthreads();
+        for (int t = tid; t < m; t += kGroupThreads) s_t[t] = start[w0 + t] + row[w0 + t];
+        __syncthreads();
+        for_group_tiles<R>(G, g, ntiles, rect, tg, [&](uint32_t t, uint32_t id) {
+            const uint32_t tw = t - (uint32_t)w0;
+            if (tw < (uint32_t)m) {
+                const uint32_t p = atomicAdd(&s_t[tw], 1u);
                 if (p < cap) vals[p] = id;
             }
         });
@@ -984,7 +1270,7 @@ __device__ uint32_t varying_bits(uint32_t a, uint32_t o, SortSmem& s)
 // is copied back, so no pass reads and writes the same buffer.  A list that
 // is not in index order (by_index) is first sorted by the triangle index, in
 // passes over its varying bytes, so the depth passes see it in index order.
-__device__ void sort_tile_large(int64_t L, uint32_t s0, uint32_t t, const float* depth,
+__device__ __forceinline__ void sort_tile_large(int64_t L, uint32_t s0, uint32_t t, const float* depth,
                                 uint32_t* vals, uint64_t* keys, uint32_t* k0, uint32_t* v0,
                                 uint32_t* k1, uint32_t* v1, SortSmem& sm, bool by_index)
 {
@@ -1164,10 +1450,10 @@ __device__ __forceinline__ void bitonic_stages(uint64_t (&x)[K], int lane)
 // Loads the L <= 64 K entries vals[b ..] as keys (pads: the largest key) and
 // sorts them with the wave's register network.
 template <int K>
-__device__ __forceinline__ void wave_sorted(int L, uint32_t b, const float* __restrict__ depth,
+__device__ __forceinline__ void wave_sorted(int lane, int L, uint32_t b,
+                                            const float* __restrict__ depth,
                                             const uint32_t* __restrict__ vals, uint64_t (&x)[K])
 {
-    const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int r = 0; r < K; ++r) {
         const int e = lane * K + r;
@@ -1181,12 +1467,13 @@ __device__ __forceinline__ void wave_sorted(int L, uint32_t b, const float* __re
 }
 
 template <int K>
-__device__ void bitonic_tile(int L, uint32_t s0, uint32_t t, const float* __restrict__ depth,
-                             uint32_t* __restrict__ vals, uint64_t* __restrict__ keys)
+__device__ __forceinline__ void bitonic_tile(int lane, int L, uint32_t s0, uint32_t t,
+                                             const float* __restrict__ depth,
+                                             uint32_t* __restrict__ vals,
+                                             uint64_t* __restrict__ keys)
 {
-    const int lane = threadIdx.x & 63;
     uint64_t x[K];
-    wave_sorted<K>(L, s0, depth, vals, x);
+    wave_sorted<K>(lane, L, s0, depth, vals, x);
 #pragma unroll
     for (int r = 0; r < K; ++r) {
         const int e = lane * K + r;
@@ -1197,15 +1484,16 @@ __device__ void bitonic_tile(int L, uint32_t s0, uint32_t t, const float* __rest
     }
 }
 
-// The wave-level sort: the smallest network that holds the tile.
-__device__ void sort_tile_bitonic(int L, uint32_t s0, uint32_t t, const float* __restrict__ depth,
-                                  uint32_t* __restrict__ vals, uint64_t* __restrict__ keys)
+// The wave-level sort: the smallest network that holds the tile (L <=
+// kWaveSortMax).
+static_assert(kWaveSortMax == 128, "networks of 64 and 128 keys");
+__device__ __forceinline__ void sort_tile_bitonic(int lane, int L, uint32_t s0, uint32_t t,
+                                                  const float* __restrict__ depth,
+                                                  uint32_t* __restrict__ vals,
+                                                  uint64_t* __restrict__ keys)
 {
-    if (L <= 64) bitonic_tile<1>(L, s0, t, depth, vals, keys);
-    else if (L <= 128) bitonic_tile<2>(L, s0, t, depth, vals, keys);
-    else if (L <= 256) bitonic_tile<4>(L, s0, t, depth, vals, keys);
-    else if (L <= 512) bitonic_tile<8>(L, s0, t, depth, vals, keys);
-    else bitonic_tile<16>(L, s0, t, depth, vals, keys);
+    if (L <= 64) bitonic_tile<1>(lane, L, s0, t, depth, vals, keys);
+    else bitonic_tile<2>(lane, L, s0, t, depth, vals, keys);
 }
 
 // The non-flip steps of strides STRIDE, STRIDE / 2, ..., 1 on a wave's 64 K
@@ -1249,10 +1537,10 @@ __device__ __forceinline__ int kv_slot(int e)
 // One merge step over the workgroup's N keys in LDS: the pairs (e, e ^ (S-1))
 // of every block of S (flip) or (e, e + S) (stride S), smaller key first.
 template <int K, bool FLIP>
-__device__ __forceinline__ void lds_step(uint64_t* __restrict__ kv, int S, int N)
+__device__ __forceinline__ void lds_step(int tid, uint64_t* __restrict__ kv, int S, int N)
 {
     const int half = FLIP ? S >> 1 : S;
-    for (int p = threadIdx.x; p < N / 2; p += kBlock) {
+    for (int p = tid; p < N / 2; p += kBlock) {
         const int off = p & (half - 1), blk = p - off;
         const int i = 2 * blk + off;
         const int j = FLIP ? 2 * blk + S - 1 - off : i + S;
@@ -1271,23 +1559,25 @@ __device__ __forceinline__ void lds_step(uint64_t* __restrict__ kv, int S, int N
 // the four runs.  Only their steps whose pairs cross waves (each level's
 // first, and stride Q of the last) go through LDS; the rest run in registers.
 template <int K>
-__device__ void sort_long_tile(int L, uint32_t s0, uint32_t t, const float* __restrict__ depth,
-                               uint32_t* __restrict__ vals, uint64_t* __restrict__ keys,
-                               uint64_t* __restrict__ kv)
+__device__ __forceinline__ void sort_long_tile(int tid, int L, uint32_t s0, uint32_t t,
+                                               const float* __restrict__ depth,
+                                               uint32_t* __restrict__ vals,
+                                               uint64_t* __restrict__ keys,
+                                               uint64_t* __restrict__ kv)
 {
     constexpr int Q = 64 * K, N = 4 * Q;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    const int w = tid >> 6, lane = tid & 63;
     const int Qa = (L + 3) >> 2;
     const int q0 = w * Qa;
     uint64_t x[K];
-    wave_sorted<K>(max(0, min(Qa, L - q0)), s0 + (uint32_t)q0, depth, vals, x);
+    wave_sorted<K>(lane, max(0, min(Qa, L - q0)), s0 + (uint32_t)q0, depth, vals, x);
     uint64_t* mine = kv + w * Q + lane * K;   // key r of this lane at mine[r ^ sw]
     const int sw = lane & (K - 1);
     // level 2Q: the flip pairs waves 0-1 and 2-3, then strides Q/2 .. 1
 #pragma unroll
     for (int r = 0; r < K; ++r) mine[r ^ sw] = x[r];
     __syncthreads();
-    lds_step<K, true>(kv, 2 * Q, N);
+    lds_step<K, true>(tid, kv, 2 * Q, N);
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < K; ++r) x[r] = mine[r ^ sw];
@@ -1296,9 +1586,9 @@ __device__ void sort_long_tile(int L, uint32_t s0, uint32_t t, const float* __re
 #pragma unroll
     for (int r = 0; r < K; ++r) mine[r ^ sw] = x[r];
     __syncthreads();
-    lds_step<K, true>(kv, 4 * Q, N);
+    lds_step<K, true>(tid, kv, 4 * Q, N);
     __syncthreads();
-    lds_step<K, false>(kv, Q, N);
+    lds_step<K, false>(tid, kv, Q, N);
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < K; ++r) x[r] = mine[r ^ sw];
@@ -1313,6 +1603,8 @@ __device__ void sort_long_tile(int L, uint32_t s0, uint32_t t, const float* __re
     }
 }
 
+constexpr int kSortGrid = 4096;   // workgroups that fill the chip several times over
+
 // Tiles taken in `order` (longest first); the first n_long of them are longer
 // than kWaveSortMax and get a whole workgroup each (four wave-level sorts of a
 // quarter each and a two-level merge up to 4 kWaveMax entries, global
@@ -1320,7 +1612,9 @@ __device__ void sort_long_tile(int L, uint32_t s0, uint32_t t, const float* __re
 // waves one tile.  The instances of a tile arrive in index order, or in any
 // order when `unordered` is set; they leave in (depth, index) order, with
 // their 64-bit keys when keys is set.
-__global__ __launch_bounds__(256) void k_tile_sort(const uint32_t* __restrict__ ranges,
+// LOOP: the grid is smaller than the work may be and walks the items.
+template <bool LOOP>
+__global__ __launch_bounds__(256, 4) void k_tile_sort(const uint32_t* __restrict__ ranges,
                                                    const uint32_t* __restrict__ order,
                                                    const uint32_t* __restrict__ n_long,
                                                    int num_tiles,
@@ -1337,36 +1631,44 @@ __global__ __launch_bounds__(256) void k_tile_sort(const uint32_t* __restrict__ 
     __shared__ TileSortSmem sm;
     const uint32_t n = d_tiles ? min(*d_tiles, (uint32_t)num_tiles) : (uint32_t)num_tiles;
     const uint32_t nl = min(*n_long, n);
-    uint32_t idx;
-    if (blockIdx.x < nl) {
-        idx = blockIdx.x;
-    } else {
-        idx = nl + (blockIdx.x - nl) * (kBlock / 64) + (threadIdx.x >> 6);
-        if (idx >= n) return;   // whole waves leave; no workgroup barrier follows
-    }
-    const uint32_t t = order[idx];
-    if (t >= (uint32_t)num_tiles) return;
-    const uint32_t s0 = ranges[2 * t];
-    const int64_t L = (int64_t)ranges[2 * t + 1] - (int64_t)s0;
-    if (blockIdx.x < nl && L > kHugeLen) {   // the whole workgroup, in global memory
-        if (!segmented)
-            sort_tile_large(L, s0, t, depth, vals, keys, k0, v0, k1, v1, sm.blk, unordered != 0);
-        return;   // else the segmented sort below takes the tile
-    }
-    if (blockIdx.x < nl) {   // the whole workgroup: four quarters and a merge
-        if (L <= 4 * 64) sort_long_tile<1>((int)L, s0, t, depth, vals, keys, sm.kv);
-        else if (L <= 4 * 128) sort_long_tile<2>((int)L, s0, t, depth, vals, keys, sm.kv);
-        else if (L <= 4 * 256) sort_long_tile<4>((int)L, s0, t, depth, vals, keys, sm.kv);
-        else if (L <= 4 * 512) sort_long_tile<8>((int)L, s0, t, depth, vals, keys, sm.kv);
-        else sort_long_tile<16>((int)L, s0, t, depth, vals, keys, sm.kv);
-        return;
-    }
-    // one wave-level sort per wave: a whole tile
-    if (L == 1) {
-        if (keys && (threadIdx.x & 63) == 0)
-            keys[s0] = tile_key(t, __float_as_uint(depth[vals[s0]]));
-    } else if (L > 1 && L <= kWaveSortMax) {
-        sort_tile_bitonic((int)L, s0, t, depth, vals, keys);
+    constexpr uint32_t kW = kBlock / 64;
+    const uint32_t items = nl + (n - nl + kW - 1) / kW;
+    for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
+        int tid = threadIdx.x;
+        // LOOP: hidden from the compiler, which else keeps every network's lane
+        // arithmetic in registers across the loop (256 VGPRs)
+        if (LOOP) asm volatile("" : "+v"(tid));
+        if (item < nl) {   // a tile of the whole workgroup (uniform branches)
+            const uint32_t t = order[item];
+            if (t < (uint32_t)num_tiles) {
+                const uint32_t s0 = ranges[2 * t];
+                const int64_t L = (int64_t)ranges[2 * t + 1] - (int64_t)s0;
+                if (L > kHugeLen) {   // in global memory, or left to the segmented sort
+                    if (!segmented)
+                        sort_tile_large(L, s0, t, depth, vals, keys, k0, v0, k1, v1, sm.blk,
+                                        unordered != 0);
+                } else if (L <= 4 * 64) sort_long_tile<1>(tid, (int)L, s0, t, depth, vals, keys, sm.kv);
+                else if (L <= 4 * 128) sort_long_tile<2>(tid, (int)L, s0, t, depth, vals, keys, sm.kv);
+                else if (L <= 4 * 256) sort_long_tile<4>(tid, (int)L, s0, t, depth, vals, keys, sm.kv);
+                else if (L <= 4 * 512) sort_long_tile<8>(tid, (int)L, s0, t, depth, vals, keys, sm.kv);
+                else sort_long_tile<16>(tid, (int)L, s0, t, depth, vals, keys, sm.kv);
+            }
+        } else {           // a tile per wave, no workgroup barrier
+            const uint32_t idx = nl + (item - nl) * kW + ((uint32_t)tid >> 6);
+            const uint32_t t = idx < n ? order[idx] : 0xffffffffu;
+            if (t < (uint32_t)num_tiles) {
+                const uint32_t s0 = ranges[2 * t];
+                const int64_t L = (int64_t)ranges[2 * t + 1] - (int64_t)s0;
+                if (L == 1) {
+                    if (keys && (tid & 63) == 0)
+                        keys[s0] = tile_key(t, __float_as_uint(depth[vals[s0]]));
+                } else if (L > 1 && L <= kWaveSortMax) {
+                    sort_tile_bitonic(tid & 63, (int)L, s0, t, depth, vals, keys);
+                }
+            }
+        }
+        if (!LOOP) return;
+        if (item + gridDim.x < nl) __syncthreads();   // the next tile reuses the LDS
     }
 }
 
@@ -1651,11 +1953,37 @@ static hipError_t radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t*
     return hipGetLastError();
 }
 
+// One workgroup per tile, or, where the host knows only a budget of tiles (a
+// batch), enough to fill the chip: they walk the tiles that there are.
+static void launch_tile_sort(const ts_bins& out, const uint32_t* order, const uint32_t* n_long,
+                             int num_tiles, const uint32_t* d_tiles, const float* depth,
+                             const BinWorkspace& ws, int segmented, int unordered,
+                             hipStream_t stream)
+{
+    auto go = [&](auto kern, int grid) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kBlock), 0, stream, out.ranges, order,
+                           n_long, num_tiles, d_tiles, depth, out.vals, out.keys, ws.tk[0],
+                           ws.tv[0], ws.tk[1], ws.tv[1], segmented, unordered);
+    };
+    if (d_tiles && num_tiles > kSortGrid) go(k_tile_sort<true>, kSortGrid);
+    else go(k_tile_sort<false>, num_tiles);
+}
+
 static int bits_for(int n)
 {
     int b = 0;
     while ((1 << b) < n) ++b;
     return b > 0 ? b : 1;
+}
+
+// Whether no group of for_group_tiles holds more entries than its 16-bit tile
+// counters can count, however many of the batch's views there are.
+static bool wide_fits(int64_t N, int64_t per_view, bool batch)
+{
+    if (!batch || per_view <= 0) return false;
+    const int64_t nv = N / per_view;   // at most
+    const int64_t gpv = nv > 0 ? kMaxGroups / nv : 0;   // fewest groups per view
+    return gpv > 0 && (per_view + gpv - 1) / gpv + 7 <= kWideEntries;
 }
 
 hipError_t run_bin_sort(const uint32_t* ntiles, const float* depth, const int16_t* rect,
@@ -1674,31 +2002,55 @@ hipError_t run_bin_sort(const uint32_t* ntiles, const float* depth, const int16_
     uint32_t* order = out.order ? out.order : ws.torder;
     uint32_t* n_long = ws.ctl + 1;
 
-    if (!seg && num_tiles > 0 && num_tiles <= kGroupTiles) {
-        // 1'. group tile counts, column scan, ranges and order, placement
+    const bool wide = num_tiles > kGroupTiles;
+    if (!seg && num_tiles > 0 && (!wide || wide_fits(N, per_view, views != nullptr))) {
+        // 1'. grouping by group tile counts
+        const uint2* r4 = reinterpret_cast<const uint2*>(rect);
+        const TileGrid tg{views, per_view, tiles_x, N, d_n};
+        const GroupOut go{out.capacity, out.ranges, order, n_long, out.d_count + 3,
+                          d_M, d_sortn, d_ovf, d_Nv};
         const int64_t want = (N + kGroupEntries - 1) / kGroupEntries;
         const int G = want < 1 ? 1 : want > kMaxGroups ? kMaxGroups : (int)want;
-        const size_t lds = 4 * (size_t)num_tiles;
-        const uint2* r4 = reinterpret_cast<const uint2*>(rect);
-        hipLaunchKernelGGL(k_group_count, dim3((unsigned)G), dim3(kGroupThreads), lds, stream,
-                           ntiles, r4, N, d_n, tiles_x, views, per_view, num_tiles, G, ws.hist,
-                           ws.blk);
-        hipLaunchKernelGGL(k_group_scan, dim3((unsigned)((num_tiles + 63) / 64)),
-                           dim3(64 * kScanWaves), 0,
-                           stream, ws.hist, num_tiles, G, ws.hl);
-        hipLaunchKernelGGL(k_group_ranges, dim3(1), dim3(kOrderThreads), lds, stream,
-                           ws.hl, num_tiles, d_tiles, (const uint32_t*)ws.blk, G,
-                           out.capacity, out.ranges, order, n_long, out.d_count + 3, d_M, d_sortn,
-                           d_ovf, d_Nv);
-        hipLaunchKernelGGL(k_group_place, dim3((unsigned)G), dim3(kGroupThreads), lds, stream,
-                           ntiles, r4, N, d_n, tiles_x, views, per_view, num_tiles, G,
-                           (const uint32_t*)ws.hist, (const uint32_t*)ws.hl, out.capacity,
-                           out.vals);
+        // runs of eight (two rounds of loads for 8192 entries) or of one (every
+        // thread has work); the line is where eight leaves half the threads idle
+        const bool eight = N / G >= 4 * kGroupThreads;
+        const size_t lds = wide ? 2 * (size_t)kWideTiles : 4 * (size_t)num_tiles;
+        const dim3 blk(kGroupThreads);
+        auto count = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)G), blk, lds, stream, ntiles, r4, tg,
+                               num_tiles, d_tiles, G, ws.hist, ws.dtot, out.ranges);
+        };
+        auto scan = [&](const uint32_t* nt) {
+            hipLaunchKernelGGL(k_group_scan, dim3((unsigned)((num_tiles + 63) / 64)),
+                               dim3(64 * kScanWaves), 0, stream, ws.hist, num_tiles, nt, G, ws.hl);
+        };
+        if (wide) {
+            count(k_group_count<8, true>);
+            scan(d_tiles);
+            hipLaunchKernelGGL(k_group_ranges_wide, dim3(1), blk, 0, stream,
+                               (const uint32_t*)ws.hl, num_tiles, d_tiles,
+                               (const uint32_t*)ws.dtot, G, go, ws.cst);
+            hipLaunchKernelGGL(k_group_place_wide<8>, dim3((unsigned)G + 1), blk, 0, stream,
+                               ntiles, r4, tg, num_tiles, d_tiles, G,
+                               (const uint32_t*)ws.hist, (const uint32_t*)ws.cst, go, out.vals);
+        } else if (N <= kOneEntries && !views) {
+            hipLaunchKernelGGL(k_bin_one, dim3(1), blk, lds, stream, ntiles, r4, tg,
+                               num_tiles, d_tiles, go, out.vals);
+        } else {
+            auto place = [&](auto kern) {
+                hipLaunchKernelGGL(kern, dim3((unsigned)G + 1), blk, lds, stream, ntiles, r4,
+                                   tg, num_tiles, d_tiles, G, (const uint32_t*)ws.hist,
+                                   (const uint32_t*)ws.hl, (const uint32_t*)ws.dtot, go, out.vals);
+            };
+            const bool fold = (int64_t)G * num_tiles <= kFoldCells;
+            if (eight) count(k_group_count<8, false>);
+            else count(k_group_count<1, false>);
+            if (!fold) scan(nullptr);
+            if (eight) fold ? place(k_group_place<8, true>) : place(k_group_place<8, false>);
+            else fold ? place(k_group_place<1, true>) : place(k_group_place<1, false>);
+        }
         // 4. depth order inside every tile
-        hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)num_tiles), dim3(kBlock), 0, stream,
-                           out.ranges, (const uint32_t*)order, (const uint32_t*)n_long, num_tiles,
-                           d_tiles, depth, out.vals, out.keys, ws.tk[0], ws.tv[0], ws.tk[1],
-                           ws.tv[1], 0, 1);
+        launch_tile_sort(out, order, n_long, num_tiles, d_tiles, depth, ws, 0, 1, stream);
         hipError_t err = hipGetLastError();
         if (err != hipSuccess || !h_count) return err;
         err = hipMemcpyAsync(h_count, out.d_count, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost,
@@ -1745,10 +2097,8 @@ hipError_t run_bin_sort(const uint32_t* ntiles, const float* depth, const int16_
     launch_tile_order(out.ranges, num_tiles, d_tiles, order, stream, n_long, out.d_count + 3);
     // 4. depth order inside every tile
     if (m_max > 0 && num_tiles > 0)
-        hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)num_tiles), dim3(kBlock), 0, stream,
-                           out.ranges, (const uint32_t*)order, (const uint32_t*)n_long, num_tiles,
-                           d_tiles, depth, out.vals, out.keys, ws.tk[0], ws.tv[0], ws.tk[1],
-                           ws.tv[1], seg ? 1 : 0, 0);
+        launch_tile_sort(out, order, n_long, num_tiles, d_tiles, depth, ws, seg ? 1 : 0, 0,
+                         stream);
     if (seg && m_max > 0 && num_tiles > 0) {
         // 4b. the huge tiles, spread over many workgroups: four stable passes
         hipLaunchKernelGGL(k_seg_plan, dim3(1), dim3(kOrderThreads), 0, stream, out.ranges,

@@ -1,0 +1,144 @@
+"""GPU tests of the binning's launch forms (one workgroup; group counts with
+the columns summed by the placing workgroups or scanned by a launch; a batch's
+windows of tiles) against a numpy sort of the instances by (tile, depth key,
+triangle index)."""
+import ctypes
+import time
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2505_19175_amd import binding as B
+from paper_2505_19175_amd import synth
+from paper_2505_19175_amd.render import Rasterizer, ViewState, scene_to_device
+from paper_2505_19175_amd.serve.executor import BatchedExecutor
+from paper_2505_19175_amd.serve.scheduler import Request
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+def _entries(seed, N, W, H):
+    """Random boxes (a third culled, most of a few pixels, some covering many
+    tiles), depth keys with ties."""
+    rng = np.random.default_rng(seed)
+    side = np.where(rng.random(N) < 0.995, rng.integers(1, 20, N), rng.integers(20, 400, N))
+    x0, y0 = rng.integers(0, W, N), rng.integers(0, H, N)
+    x1, y1 = np.minimum(x0 + side, W - 1), np.minimum(y0 + side // 2, H - 1)
+    nt = (x1 // 16 - x0 // 16 + 1) * (y1 // 16 - y0 // 16 + 1)
+    gone = rng.random(N) < 0.33
+    nt[gone] = 0
+    rect = np.stack([x0, x1, y0, y1], 1).astype(np.int16)
+    rect[gone] = (0, -1, 0, -1)
+    depth = (rng.integers(0, max(2, N // 3), N) * np.float32(1e-3) + 1).astype(np.float32)
+    return rect, nt.astype(np.int32), depth
+
+
+def _reference(rect, nt, depth, tiles_x):
+    e = np.repeat(np.arange(len(nt)), nt)
+    k = np.arange(len(e)) - np.repeat(np.cumsum(nt) - nt, nt)
+    r = rect.astype(np.int64)[e] // 16
+    nx = r[:, 1] - r[:, 0] + 1
+    tile = (r[:, 2] + k // nx) * tiles_x + r[:, 0] + k % nx
+    order = np.lexsort((e, depth[e], tile))
+    return tile[order], e[order]
+
+
+def _bin(rect, nt, depth, W, H, capacity, sync=True):
+    N = len(nt)
+    st = ViewState(N, W, H, capacity, device=DEV, keys=True)
+    st.rect[:N].copy_(torch.as_tensor(rect))
+    st.ntiles[:N].copy_(torch.as_tensor(nt))
+    st.depth_key[:N].copy_(torch.as_tensor(depth))
+    cam = B.make_camera(synth.identity_camera(W, H))
+    count = (ctypes.c_uint32 * 2)() if sync else None
+    B.ts_bin_sort(st.proj, N, cam, st.ws, st.ws_bytes, st.bins, count,
+                  torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return st, count
+
+
+# one workgroup up to 4096 entries (4, 1023, 4096); groups with folded columns
+# (4097: 5 groups of 920 tiles; 20011: 20 of 256) or a column scan (70001: 69 of
+# 3600); runs of eight from 4096 entries per group (1200007: 4688); the last
+# size also in a 1600x1040 view and in one of a single tile row
+@pytest.mark.parametrize("N,W,H", [(1, 16, 16), (4, 130, 40), (1023, 640, 360), (4096, 640, 360),
+                                   (4097, 640, 360), (20_011, 256, 256), (70_001, 1280, 720),
+                                   (1_200_007, 1600, 1040), (1_200_007, 2047, 16)])
+def test_instances_in_tile_depth_index_order(N, W, H):
+    rect, nt, depth = _entries(N + W, N, W, H)
+    tiles_x = (W + 15) // 16
+    tile, vals = _reference(rect, nt, depth, tiles_x)
+    M = len(vals)
+    st, count = _bin(rect, nt, depth, W, H, max(M, 1))
+    assert (count[0], count[1]) == (M, int((nt > 0).sum()))
+    np.testing.assert_array_equal(st.vals[:M].cpu().numpy(), vals)
+    want = (tile.astype(np.uint64) << np.uint64(32)) | depth[vals].view(np.uint32)
+    np.testing.assert_array_equal(st.keys[:M].cpu().numpy().view(np.uint64), want)
+    T = st.num_tiles
+    lens = np.bincount(tile, minlength=T)
+    ends = np.cumsum(lens)
+    ranges = np.stack([ends - lens, ends], 1)
+    ranges[lens == 0] = 0
+    np.testing.assert_array_equal(st.ranges.cpu().numpy(), ranges)
+    order = st.order.cpu().numpy()
+    np.testing.assert_array_equal(np.sort(order), np.arange(T))
+    # longest first, lengths of 2047 and more in any order
+    assert (np.diff(np.minimum(lens[order], 2047)) <= 0).all()
+    assert st.d_count.cpu().tolist() == [M, int((nt > 0).sum()), 0, int((lens > 4096).sum())]
+
+
+@pytest.mark.parametrize("N,W,H", [(3000, 640, 360), (20_011, 256, 256), (70_001, 1280, 720)])
+def test_overflow_keeps_sorted_runs(N, W, H):
+    """With room for half the instances the flag is set, the ranges are
+    clamped, and each run holds entries of its tile in order."""
+    rect, nt, depth = _entries(N, N, W, H)
+    tiles_x = (W + 15) // 16
+    tile, vals = _reference(rect, nt, depth, tiles_x)
+    cap = len(vals) // 2
+    st, _ = _bin(rect, nt, depth, W, H, cap, sync=False)
+    d = st.d_count.cpu().tolist()
+    assert d[0] == len(vals) and d[2] == 1
+    r, got = st.ranges.cpu().numpy(), st.vals.cpu().numpy()
+    assert r[:, 1].max() == cap and (r[:, 1] - r[:, 0]).sum() == cap
+    every = set(zip(tile.tolist(), vals.tolist()))
+    for t in np.flatnonzero(r[:, 1] > r[:, 0])[:: max(1, len(r) // 200)]:
+        run = got[r[t, 0]:r[t, 1]]
+        assert all((int(t), int(v)) in every for v in run)
+        assert (np.lexsort((run, depth[run])) == np.arange(len(run))).all()
+
+
+# a batch's tiles in one window (two 360p views), in two (three 1080p views:
+# 24480 of 16384 a window), a budget under 12288 tiles (32-bit counters), and
+# more views than a group's share of a soup of 40
+@pytest.mark.parametrize("n,sizes,budget", [
+    (30_000, [(640, 360), (640, 360)], 65_280),
+    (30_000, [(1920, 1080), (1920, 1079), (1919, 1080)], 65_280),
+    (30_000, [(640, 360), (333, 200), (64, 48)], 4000),
+    (40, [(64 + 16 * i, 48) for i in range(6)], 20_000)])
+def test_batch_windows_equal_single_views(n, sizes, budget):
+    rng = np.random.Generator(np.random.PCG64(5))
+    sc = synth.cluster_soup(5, n, extent=3.0, std=0.4, edge_median=0.05, sh_degree=1, rng=rng)
+    cfg = synth.Config(sh_degree=1)
+    scene = scene_to_device(sc, DEV)
+    cams = [synth.look_at(e, width=w, height=h)
+            for e, (w, h) in zip(synth.hemisphere_eyes(rng, len(sizes)), sizes)]
+    ex = BatchedExecutor(scene, cfg, time.perf_counter, max_views=len(sizes) + 1,
+                         max_tiles=budget, max_pixels=sum(w * h for w, h in sizes),
+                         capacity=1 << 21, slots=1)
+    for views in (len(sizes), 1, len(sizes)):        # replays with other views
+        batch = [Request(i, c, 0.0) for i, c in enumerate(cams[:views])]
+        ex.submit(0, batch)
+        while (res := ex.poll(0)) is None:
+            pass
+        assert not res.overflow
+        total = 0
+        for cam, (rgb, alpha, depth) in zip(cams, ex.outputs(0, batch)):
+            st = ViewState(n, cam.width, cam.height, 1 << 20)
+            out = Rasterizer(cfg).forward(st, scene, cam, sync=True)
+            total += st.M
+            for a, b in ((rgb, out.rgb), (alpha, out.alpha), (depth, out.depth)):
+                assert torch.equal(a, b)
+        assert res.instances == total
