@@ -136,3 +136,38 @@ def test_densify_3m_soup():
     assert d[0] == M
     assert np.array_equal(gv[:M], wv) and np.array_equal(go[:M], wo)
     assert np.array_equal(gs[:M], ws_) and np.array_equal(gsh[:M], wsh)
+
+
+# Around the subdivision's chunk (512 triangles, 2048 above 2^18) and its
+# batches of 256 selected ones, with every triangle, none, or some selected;
+# degrees whose SH rows are (1, 3) and are not (0, 2) whole 16-byte vectors.
+@pytest.mark.parametrize("N,deg,share", [(511, 3, 1.0), (512, 2, 1.0), (513, 1, 1.0),
+                                         (4097, 0, 0.3), (6150, 3, 0.0), (257, 3, 1.0),
+                                         (1 << 18, 1, 0.1), ((1 << 18) + 1, 1, 1.0),
+                                         ((1 << 18) + 2047, 0, 0.3), ((1 << 18) + 2048, 2, 0.1)])
+def test_subdivide_chunk_edges(N, deg, share):
+    v, o, s, sh = _soup(31, N, deg)
+    sel = np.random.default_rng(32).random(N) < share
+    n = int(sel.sum())
+    gv, go, gs, gsh, d = _subdivide(v, o, s, sh, deg, sel, N + 3 * n)
+    wv, wo, ws_, wsh = D.subdivide(v, o, s, sh, sel)
+    assert d[0] == N + 3 * n and d[1] == 0
+    for got, want in ((gv, wv), (go, wo), (gs, ws_), (gsh, wsh)):
+        assert np.array_equal(got, want)
+
+
+def test_select_from_unaligned_arrays():
+    """Slices that start 4 (and 1) bytes into an array: element-wise loads."""
+    rng = np.random.default_rng(33)
+    N = 5001
+    o, u = (rng.random(N + 1).astype(np.float32) for _ in range(2))
+    ws_bytes = B.ts_densify_workspace_bytes(N)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+    sel = torch.zeros(N + 1, dtype=torch.uint8, device=DEV)
+    B.ts_densify_select(_t(o)[1:], _t(o)[1:], N, B.TS_DENSIFY_OPACITY, 700.0, _t(u)[1:], sel[1:],
+                        ws, ws_bytes)
+    torch.cuda.synchronize()
+    got = sel.cpu().numpy()
+    assert got[0] == 0
+    assert np.array_equal(got[1:].astype(bool), _select(o[1:], o[1:], B.TS_DENSIFY_OPACITY, 700.0,
+                                                        u[1:]))
