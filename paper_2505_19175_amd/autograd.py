@@ -20,7 +20,7 @@ from __future__ import annotations
 import torch
 from torch.autograd.function import once_differentiable
 
-from .render import Rasterizer, ViewState
+from .render import Outputs, Rasterizer, ViewState
 
 
 def _check_inputs(v, o, sigma, sh, cfg):
@@ -57,7 +57,9 @@ class TriangleRasterize(torch.autograd.Function):
         st = ViewState(N, cam.width, cam.height, cap, device=v.device)
         ras = Rasterizer(cfg, device=v.device)
         out = ras.forward(st, scene_t, cam, sync=True)
-        ctx.state = (ras, st, scene_t, out)
+        # only what the backward reads: an image kept here would hold its own
+        # graph node, and the view's buffers would wait for the cycle collector
+        ctx.state = (ras, st, scene_t, Outputs(None, None, None, out.T_final, out.last))
         ctx.dtypes = tuple(t.dtype for t in (v, o, sigma, sh))
         return out.rgb, out.alpha, out.depth
 
@@ -67,7 +69,9 @@ class TriangleRasterize(torch.autograd.Function):
         ras, st, scene_t, out = ctx.state
         if g_rgb is None and g_alpha is None and g_depth is None:
             return None, None, None, None, None, None, None
-        dC = (g_rgb if g_rgb is not None else torch.zeros_like(out.rgb)).contiguous().float()
+        if g_rgb is None:
+            g_rgb = out.T_final.new_zeros((3,) + tuple(out.T_final.shape))
+        dC = g_rgb.contiguous().float()
         dA = None if g_alpha is None else g_alpha.contiguous().float()
         dD = None if g_depth is None else g_depth.contiguous().float()
         # the library leaves the per-triangle accumulators zeroed after each

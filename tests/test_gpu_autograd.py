@@ -132,3 +132,35 @@ def test_autograd_rejects_bad_inputs():
         rasterize(v, o.detach().cpu(), s, sh, cam, cfg)
     with pytest.raises(ValueError):        # vertices not [N,3,3]
         rasterize(v.reshape(-1, 9), o, s, sh, cam, cfg)
+
+
+def test_lists_grow_and_state_is_freed():
+    """A capacity hint far below the view's instances: the forward grows the
+    lists and renders again, with the same images and gradients; and once the
+    outputs are gone nothing keeps the view's buffers alive (no cycle through
+    the graph)."""
+    import gc
+    sc, cfg = synth.workload_small().scene, synth.Config(sh_degree=0)
+    cam = synth.identity_camera(128, 128)
+    par = [torch.tensor(a, device="cuda:0", requires_grad=True)
+           for a in (sc.v, sc.o, sc.sigma, sc.sh)]
+    ref = rasterize(*par, cam, cfg)
+    got = rasterize(*par, cam, cfg, 7)
+    for a, b in zip(ref, got):
+        assert torch.equal(a, b)
+    gr, gg = (torch.autograd.grad(x[0].sum(), par) for x in (ref, got))
+    for a, b in zip(gr, gg):
+        assert torch.allclose(a, b, rtol=1e-4, atol=1e-6 * float(a.abs().max()))
+    del ref, got, gr, gg
+    gc.collect()
+    gc.disable()
+    try:
+        torch.cuda.synchronize()
+        before = torch.cuda.memory_allocated()
+        for _ in range(3):
+            rgb, _, _ = rasterize(*par, cam, cfg)
+            g = torch.autograd.grad(rgb.sum(), par)
+            del rgb, _, g
+        assert torch.cuda.memory_allocated() == before
+    finally:
+        gc.enable()
