@@ -139,3 +139,16 @@ def test_batched_serving_equals_alone(window):
     for (rgb, a, d), (want_rgb, want_a) in zip(ex.outputs(0, batch), alone):
         np.testing.assert_array_equal(rgb.cpu().numpy(), want_rgb)
         np.testing.assert_array_equal(a.cpu().numpy(), want_a)
+
+
+# One tile whose list ends just before, at and after the sigmoid backward's
+# batch of 128 entries (and two batches), faint enough that every entry is
+# composited: the sums in LDS of a full, a partial and a following batch.
+@pytest.mark.parametrize("n", [127, 128, 129, 257])
+def test_sigmoid_batches(n):
+    sc, cam = _soup64(45, n, W=16, H=16, size=0.5, deg=1, sigma=(0.5, 2.0), o=(0.02, 0.06),
+                      dtype=np.float32)
+    nvis, M, n_ok, n_flag, worst, s = _full(sc, cam, Config(sh_degree=1, window=WINDOW_SIGMOID),
+                                            202)
+    assert M == nvis == n
+    print(n, n_ok, n_flag, worst, s)
