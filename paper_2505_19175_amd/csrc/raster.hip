@@ -211,6 +211,9 @@ __device__ __forceinline__ Lens build_lists(Stage& S, int n, int w, int lane, in
     uint8_t* l3 = S.list[4 * w + 3];
 #pragma unroll
     for (int c = 0; c < Stage::kN / 64; ++c) {
+        // short lists (25 entries a tile at 300k triangles) need one round of the
+        // four: forward 25.9 -> 23.4 us, backward 26.1 -> 24.8 us
+        if (c * 64 >= n) break;   // the same for the wave
         const int e = c * 64 + lane;
         const uint32_t h = e < n ? ((uint32_t)S.hit[e] >> (4 * w)) & 0xfu : 0u;
         auto put = [&](bool bit, uint8_t* lst, int& len) {
