@@ -562,24 +562,40 @@ __global__ __launch_bounds__(256) void k_raster_fwd_queue(
 // transpose-and-add: each step pairs lanes across one bit of the lane index
 // within the row (row_ror:8, row_half_mirror, quad_perm) and each lane keeps
 // the half of its values its partner sends it, so the values per lane halve.
-// 45 VALU, no LDS.  On return lane i of a row holds the row total of slot i.
+// 33 VALU, no LDS.  On return lane i of a row holds the row total of slot i.
+//
+// The first two steps split the row by whole banks of four lanes, so the bank
+// mask of a DPP add writes one half of the lanes from one value and a second
+// add the other half from the other: two adds where a select of what to keep,
+// one of what to send and an add stood (45 VALU; the same sums).  Inline
+// assembly, since the compiler forms DPP adds of full masks only; a DPP
+// operand has to be written two instructions before it is read, hence the
+// s_nop ahead of each group (inside the groups the distances are larger).
+// Raster backward of 3M triangles 158 -> 153 us, sigmoid window 501 -> 482 us.
+#define TS_ADD8(d, x, y)                                                    \
+    "v_add_f32_dpp %" #d ", %" #x ", %" #x " row_ror:8 row_mask:0xf bank_mask:0x3\n\t" \
+    "v_add_f32_dpp %" #d ", %" #y ", %" #y " row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+#define TS_ADD4(d, x, y)                                                    \
+    "v_add_f32_dpp %" #d ", %" #x ", %" #x " row_half_mirror row_mask:0xf bank_mask:0x5\n\t" \
+    "v_add_f32_dpp %" #d ", %" #y ", %" #y " row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+
 __device__ __forceinline__ float row_reduce16(const float (&v)[16], int i)
 {
     float a8[8], a4[4], a2[2];
-    const bool b3 = i & 8;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const float send = b3 ? v[k] : v[k + 8];
-        const float keep = b3 ? v[k + 8] : v[k];
-        a8[k] = keep + dpp<0x128>(send);           // row_ror:8      (partner i ^ 8)
-    }
-    const bool b2 = i & 4;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float send = b2 ? a8[k] : a8[k + 4];
-        const float keep = b2 ? a8[k + 4] : a8[k];
-        a4[k] = keep + dpp<0x141>(send);           // row_half_mirror (partner i ^ 7)
-    }
+    // partner i ^ 8: lanes 0-7 of the row sum slots 0-7, lanes 8-15 slots 8-15
+    asm("s_nop 1\n\t"
+        TS_ADD8(0, 8, 16) TS_ADD8(1, 9, 17) TS_ADD8(2, 10, 18) TS_ADD8(3, 11, 19)
+        TS_ADD8(4, 12, 20) TS_ADD8(5, 13, 21) TS_ADD8(6, 14, 22) TS_ADD8(7, 15, 23)
+        : "=&v"(a8[0]), "=&v"(a8[1]), "=&v"(a8[2]), "=&v"(a8[3]), "=&v"(a8[4]), "=&v"(a8[5]),
+          "=&v"(a8[6]), "=&v"(a8[7])
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]),
+          "v"(v[8]), "v"(v[9]), "v"(v[10]), "v"(v[11]), "v"(v[12]), "v"(v[13]), "v"(v[14]),
+          "v"(v[15]));
+    // partner i ^ 7, within each half by bit 2
+    asm("s_nop 1\n\t" TS_ADD4(0, 4, 8) TS_ADD4(1, 5, 9) TS_ADD4(2, 6, 10) TS_ADD4(3, 7, 11)
+        : "=&v"(a4[0]), "=&v"(a4[1]), "=&v"(a4[2]), "=&v"(a4[3])
+        : "v"(a8[0]), "v"(a8[1]), "v"(a8[2]), "v"(a8[3]), "v"(a8[4]), "v"(a8[5]), "v"(a8[6]),
+          "v"(a8[7]));
     const bool b1 = i & 2;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
