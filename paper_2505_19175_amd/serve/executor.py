@@ -35,14 +35,22 @@ class _Slot:
     pass
 
 
-def _deliver(rgb, alpha, depth, d2h: bool):
-    """Copies of one view's outputs that the request owns, enqueued on the
-    current stream (the one that rendered them)."""
+def _deliver(frames, d2h: bool):
+    """Per frame (rgb, alpha, depth), copies that its request owns, enqueued on
+    the current stream (the one that rendered them).  All frames of a batch
+    are copied in one launch instead of three per view (two batches of four
+    mixed views: 987 -> 967 us)."""
     if d2h:
-        host = torch.empty(rgb.shape, dtype=torch.float32, pin_memory=True)
-        host.copy_(rgb, non_blocking=True)
-        return (host, None, None)
-    return (rgb.clone(), alpha.clone(), depth.clone())
+        out = []
+        for rgb, _, _ in frames:
+            host = torch.empty(rgb.shape, dtype=torch.float32, pin_memory=True)
+            host.copy_(rgb, non_blocking=True)
+            out.append((host, None, None))
+        return out
+    src = [t for f in frames for t in f]
+    dst = [torch.empty_like(t) for t in src]
+    torch._foreach_copy_(dst, src)
+    return [tuple(dst[i:i + 3]) for i in range(0, len(dst), 3)]
 
 
 class BatchedExecutor:
@@ -139,11 +147,8 @@ class BatchedExecutor:
                 s.graph.replay()
             else:
                 self._launch(s, s.stream.cuda_stream)
-            for i, r in enumerate(batch):
-                po, W, H = int(views[i].pixel_offset), r.camera.width, r.camera.height
-                r.result = _deliver(s.rgb[3 * po: 3 * po + 3 * W * H].view(3, H, W),
-                                    s.alpha[po: po + W * H].view(H, W),
-                                    s.depth[po: po + W * H].view(H, W), self.d2h)
+            for r, got in zip(batch, _deliver(self._frames(s, views, batch), self.d2h)):
+                r.result = got
             s.event.record(s.stream)
             s.count_host.copy_(s.d_count, non_blocking=True)
 
@@ -161,8 +166,11 @@ class BatchedExecutor:
     def outputs(self, slot: int, batch: List[Request]):
         """Per-request (rgb [3,H,W], alpha, depth) views into the slot's
         buffers (valid until the slot's next submission)."""
-        s = self._slots[slot]
         views, _, _ = self.layout(batch)
+        return self._frames(self._slots[slot], views, batch)
+
+    @staticmethod
+    def _frames(s, views, batch):
         out = []
         for i, r in enumerate(batch):
             po, W, H = int(views[i].pixel_offset), r.camera.width, r.camera.height
@@ -200,7 +208,7 @@ class PlainExecutor:
         (r,) = batch
         st, out = self._state(r.camera.width, r.camera.height)
         self.ras.forward(st, self.scene_t, r.camera, out=out, sync=True)
-        r.result = _deliver(out.rgb, out.alpha, out.depth, self.d2h)
+        (r.result,) = _deliver([(out.rgb, out.alpha, out.depth)], self.d2h)
         self.event.record()
         self.batch = batch
         self.last = (st, out)
