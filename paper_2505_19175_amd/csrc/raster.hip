@@ -1,20 +1,29 @@
 // raster.hip -- per-tile compositing on gfx950: forward (front to back) and
 // backward (back to front, transmittance recovered from the final value).
 //
-// One 256-thread workgroup per 16x16 tile.  Wave w owns the 8x8 quadrant
-// (w & 1, w >> 1) and each of its four 16-lane rows (a DPP row) owns a 4x4
-// block of it: lane l shades pixel (l & 3, (l >> 2) & 3) of block
-// g = l >> 4 = (g & 1, g >> 1).
+// One 256-thread workgroup per 16x16 tile.  The tile's list is walked in
+// batches of 256 entries staged through LDS: each thread copies one record as
+// six 16-byte chunks and its depth into chunk-major arrays (consecutive lanes
+// write consecutive slots: no bank conflicts) and marks the cells of the tile
+// that can hold a pixel it composites.  Every cell walks its own list of byte
+// indices of the batch's entries, so a pixel never evaluates a triangle that
+// misses its cell; the lists live in LDS and are read one byte per lane per
+// step: no scalar list bookkeeping.  The walk is bound by vector instructions,
+// so what counts is the number of wave steps: the longest of a wave's lists.
 //
-// The tile's list is walked in batches of 256 entries staged through LDS:
-// each thread copies one record as six 16-byte chunks and its depth into
-// chunk-major arrays (consecutive lanes write consecutive slots: no bank
-// conflicts) and marks the 4x4 blocks of the tile that can hold a pixel it
-// composites.  Each wave then writes, for each of its four blocks, the byte
-// indices of the batch entries marked for it (ballot + mbcnt compaction), so
-// every row walks its own list -- one wave step advances four lists, and a
-// row never evaluates a triangle that misses its block.  The lists live in
-// LDS and are read one byte per lane per step: no scalar list bookkeeping.
+// Forward: the cells are the 64 pixel quads (2x2 pixels), in rows of eight,
+// 16 to a wave; lane 4 q + i shades pixel i of quad q.  Each lane has the
+// quads of its entry as 64 bits, which the wave transposes, so lane q of the
+// wave that walks quad q has the entries (wave w stages entries 64 w on).
+// Against 4x4 blocks, four to a wave: a triangle of the 3M view covers 3-4
+// pixels, which 16 lanes evaluate; 720p forward 113.7 -> 76.6 us (vector
+// instructions 46.4M -> 29.9M), 1040p 160 -> 109, 300k 23.3 -> 20.8, 20k at
+// 256x256 28.3 -> 22.1, sigmoid window 250 -> 210, LogSumExp 37.1 -> 32.2.
+//
+// Backward: the cells are 4x4 blocks.  Wave w owns the 8x8 quadrant (w & 1,
+// w >> 1) and each of its four 16-lane rows (a DPP row) a 4x4 block of it:
+// lane l shades pixel (l & 3, (l >> 2) & 3) of block g = l >> 4 = (g & 1,
+// g >> 1), and a row sums an entry's gradients over its 16 pixels.
 //
 // The window is evaluated as three FP64 affine functions per pixel (gfx950
 // issues v_fma_f64 at the rate of unpacked v_fma_f32); the rest is FP32,
@@ -41,13 +50,6 @@ struct StageExtra<TS_WINDOW_LSE, NB> {
     float ps[NB];
 };
 
-// The forward that keeps pruning statistics gathers them per batch entry in
-// words the plain forward does not need during its walk, so its LDS stays at
-// 25 allocation units: the largest T*o (float bits; non-negative floats
-// order as integers) in the triangle-index words, the composited pixels as
-// 16-bit halves of the per-entry block-hit words (dead once every wave has
-// built its lists).  One global max and one add per entry and tile flush
-// them at the end of the batch.
 template <int WIN, int NB>
 struct StageBase : StageExtra<WIN, NB> {
     static constexpr int kN = NB;
@@ -57,10 +59,30 @@ struct StageBase : StageExtra<WIN, NB> {
     uint8_t list[16][NB];    // per block 4 w + g: its entries of the batch, in order
 };
 
-template <int WIN, bool ST = false>
-struct StageT : StageBase<WIN, kBatch> {
-    uint32_t comp[kBatch / 2];   // forward: blocks where each entry composited, 16 bits each
-    uint32_t tri[kBatch];        // triangle (entry) index of each staged entry
+// The forward's LDS.  mask[.][c][q]: which of the batch's entries 64 c ..
+// 64 c + 63 quad q may composite (low and high word); words: the lists of the
+// four waves, those of a wave's quads one after another, then a word per entry.
+//
+// The forward that keeps pruning statistics gathers them per batch entry in
+// words that are free during its walk: the largest T*o (float bits;
+// non-negative floats order as integers) in the entries' words, the blocks
+// where they composited and their composited pixels as 16-bit halves of the
+// masks (dead once every wave has read them).  One global max and one add per
+// entry and tile flush them at the end of the batch.
+constexpr int kWaveList = 1024;   // entries of a wave's lists: one word of masks always fits
+
+template <int WIN>
+struct FwdStage : StageExtra<WIN, kBatch> {
+    static constexpr int kN = kBatch;
+    float4 q[kChunks][kBatch];
+    uint32_t mask[2][kBatch / 64][64];
+    uint32_t words[kWaveList + kBatch];
+
+    // the lists of wave w; an idle lane may read up to kBatch bytes past their
+    // end, in the next wave's lists or the entries' words, and uses nothing of it
+    __device__ uint8_t* list(int w) { return reinterpret_cast<uint8_t*>(words) + w * kWaveList; }
+    // a word per staged entry
+    __device__ uint32_t* tri() { return words + kWaveList; }
 };
 
 // The backward's LDS.  Sigmoid window: its triangles cover most blocks of many
@@ -182,13 +204,135 @@ __device__ __forceinline__ uint32_t stage_rec(Stage& S, const TriRecord* __restr
     return m;
 }
 
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x)
+{
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
+
+// Bits [lo, hi] of eight, none if the interval misses them.
+__device__ __forceinline__ uint32_t span8(int lo, int hi)
+{
+    lo = max(lo, 0);
+    hi = min(hi, 7);
+    return lo <= hi ? (2u << hi) - (1u << lo) : 0u;
+}
+
+// Copy record `tri` into LDS slot threadIdx.x and return the tile's quads
+// (bit 8 y + x) that may hold a composited pixel of it: the tight box touches
+// the quad, and for every edge k the largest u_k over the quad's four pixel
+// centres reaches ut (the separating axes of stage_rec's test).
+//
+// Along a row of quads A X + (B Y + K) >= 0 is a half line, so an edge costs
+// one FMA, a clamp, a conversion and a shift for eight quads.  In FP32: the
+// slack of 2^-16 S, S = |C| + 16 (|A| + |B|), covers the coefficients' and
+// this evaluation's rounding (2^-21 S) and the floor under |A| that keeps the
+// slope finite (28 2^-22 S over the tile), and loses no selectivity to speak
+// of (a thousandth of u).  A sum that FP32 cannot hold keeps every quad; a
+// NaN keeps none.
+struct Quads {
+    uint32_t lo, hi;
+};
+
+template <class Stage>
+__device__ __forceinline__ Quads stage_quads(Stage& S, const TriRecord* __restrict__ rec,
+                                             uint32_t tri, int tx0, int ty0)
+{
+    const float4* src = reinterpret_cast<const float4*>(rec + tri);
+    RecView u;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) u.q[c] = src[c];
+    const uint32_t cx = span8((u.r.px0 - tx0) >> 1, (u.r.px1 - tx0) >> 1);
+    const uint32_t cy = span8((u.r.py0 - ty0) >> 1, (u.r.py1 - ty0) >> 1);
+    const float ut = u.r.ut;
+    write_stage<true>(S, u, tx0, ty0);   // makes C tile-relative
+    uint32_t row[8];
+#pragma unroll
+    for (int y = 0; y < 8; ++y) row[y] = cx & (uint32_t)__builtin_amdgcn_sbfe((int)cy, y, 1);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const float A = (float)u.r.A[k], B = (float)u.r.B[k], C = (float)u.r.C[k];
+        const float sum = fabsf(C) + 16.f * (fabsf(A) + fabsf(B));
+        // A X + B Y + K at quad (X, Y)'s largest pixel centre, pixels 2 X, 2 Y on
+        const float K = C - ut + 0x1p-16f * sum + fmaxf(A, 0.f) + fmaxf(B, 0.f);
+        const float inv = __builtin_amdgcn_rcpf(2.f * fmaxf(fabsf(A), fmaf(0x1p-22f, sum, 1e-30f)));
+        const bool neg = A < 0.f;          // X < t, else X > t
+        const float si = neg ? inv : -inv;
+        const bool big = !(sum < 1e30f);
+        const float slope = big ? 0.f : 2.f * B * si;
+        const float t0 = big ? (neg ? 9.f : 0.f) : fmaf(K, si, 1.f);
+        const uint32_t flip = neg ? 0xffu : 0u;
+        const uint32_t nan = sum == sum ? 0xffu : 0u;
+#pragma unroll
+        for (int y = 0; y < 8; ++y) {
+            const float t = __builtin_amdgcn_fmed3f(fmaf(slope, (float)y, t0), 0.f, 8.f);
+            row[y] &= ((0xffu << (uint32_t)t) ^ flip) & nan;
+        }
+    }
+    return Quads{row[0] | (row[1] << 8) | (row[2] << 16) | (row[3] << 24),
+                 row[4] | (row[5] << 8) | (row[6] << 16) | (row[7] << 24)};
+}
+
+// Transpose the wave's 64x64 bits: lane l gives the quads of entry l, lane q
+// receives the entries of quad q.  Six exchanges with lane l ^ s, s = 32 .. 1,
+// each of which swaps bit s of the row index and of the column index; 40 VALU,
+// where 64 ballots would take several each.
+__device__ __forceinline__ void transpose64(uint32_t& lo, uint32_t& hi, int lane)
+{
+    {
+        const auto t = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+        lo = t[0];
+        hi = t[1];
+    }
+    const uint32_t s16 = lane & 16 ? 0x07060302u : 0x05040100u;
+    const uint32_t s8 = lane & 8 ? 0x03070105u : 0x06020400u;
+    auto step16 = [&](uint32_t x) {
+        const auto t = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return __builtin_amdgcn_perm(t[1], t[0], s16);
+    };
+    auto bits = [&](uint32_t x, uint32_t t, int s, uint32_t M) {
+        const bool up = lane & s;
+        const uint32_t rot = __builtin_amdgcn_alignbit(t, t, up ? s : 32 - s);
+        const uint32_t take = up ? M : ~M;
+        return (rot & take) | (x & ~take);
+    };
+    auto rest = [&](uint32_t x) {
+        x = __builtin_amdgcn_perm(dpp_u<0x128>(x), x, s8);             // lane ^ 8
+        x = bits(x, dpp_u<0x1B>(dpp_u<0x141>(x)), 4, 0x0f0f0f0fu);     // lane ^ 7 ^ 3
+        x = bits(x, dpp_u<0x4E>(x), 2, 0x33333333u);
+        return bits(x, dpp_u<0xB1>(x), 1, 0x55555555u);
+    };
+    lo = rest(step16(lo));
+    hi = rest(step16(hi));
+}
+
+// Inclusive sum over the wave's lanes.
+__device__ __forceinline__ int wave_scan(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31
+    return x;
+}
+
 template <bool ZA = false, class Stage>
 __device__ __forceinline__ TriRecord read_rec(const Stage& S, int j)
 {
     RecView u;
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) u.q[c] = S.q[c][j];
-    u.r.z = ZA ? u.q[4].z : S.z[j];
+    if constexpr (ZA) u.r.z = u.q[4].z;
+    else u.r.z = S.z[j];
     if constexpr (Stage::kLse) u.r.phis = S.ps[j];
     return u.r;
 }
@@ -217,7 +361,7 @@ __device__ __forceinline__ Lens build_lists(Stage& S, int n, int w, int lane, in
         const int e = c * 64 + lane;
         const uint32_t h = e < n ? ((uint32_t)S.hit[e] >> (4 * w)) & 0xfu : 0u;
         auto put = [&](bool bit, uint8_t* lst, int& len) {
-            const uint64_t m = __ballot(bit);
+            const uint64_t m = ballot64(bit);
             const uint32_t below = __builtin_amdgcn_mbcnt_hi(
                 (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
             if (bit) lst[len + (int)below] = (uint8_t)e;
@@ -299,28 +443,11 @@ __device__ __forceinline__ Pix pixel_of(int tx, int ty)
     return P;
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x)
+// Largest value over the four lanes of each pixel quad.
+__device__ __forceinline__ float quad_max_f(float x)
 {
-    return __builtin_bit_cast(
-        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
-}
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u(uint32_t x)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
-}
-
-// Largest value over the 16 lanes of each DPP row (quad swaps, then the
-// half-row and row mirrors).
-__device__ __forceinline__ float row_max_f(float x)
-{
-    x = fmaxf(x, dpp<0xB1>(x));    // quad_perm [1,0,3,2]
-    x = fmaxf(x, dpp<0x4E>(x));    // quad_perm [2,3,0,1]
-    x = fmaxf(x, dpp<0x141>(x));   // row_half_mirror
-    x = fmaxf(x, dpp<0x140>(x));   // row_mirror
-    return x;
+    x = fmaxf(x, dpp<0xB1>(x));      // quad_perm [1,0,3,2]
+    return fmaxf(x, dpp<0x4E>(x));   // quad_perm [2,3,0,1]
 }
 
 // ---------------------------------------------------------------------------
@@ -355,11 +482,13 @@ struct TileJob {
 template <int WIN, bool ST, int FS = 0>
 __device__ __forceinline__ void fwd_tile(const TriRecord* __restrict__ rec,
                                          const uint32_t* __restrict__ vals, const Cfg& cfg,
-                                         const TileJob& J, StageT<WIN, ST>& S)
+                                         const TileJob& J, FwdStage<WIN>& S)
 {
-    const int tid = threadIdx.x, lane = tid & 63;
-    const Pix P = pixel_of(J.tx, J.ty);
-    const bool inside = P.px < J.W && P.py < J.H;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int qi = lane >> 2, i = lane & 3;   // quad of the wave, pixel of the quad
+    const int lx = 2 * (qi & 7) + (i & 1), ly = 4 * w + 2 * (qi >> 3) + (i >> 1);
+    const int px = J.tx * kTile + lx, py = J.ty * kTile + ly;
+    const bool inside = px < J.W && py < J.H;
     const uint32_t start = J.start, end = J.end;
 
     float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, D = 0.f;
@@ -367,105 +496,146 @@ __device__ __forceinline__ void fwd_tile(const TriRecord* __restrict__ rec,
     bool done = !inside;
     uint32_t fcnt = 0, foff = 0;
     if constexpr (FS == 2) {
-        if (inside) foff = J.foffs[(int64_t)P.py * J.W + P.px];
+        if (inside) foff = J.foffs[(int64_t)py * J.W + px];
     }
 
-    const uint32_t my_bit = 1u << (4 * P.w + P.g);
-    const double dxt = (double)(P.px - J.tx * kTile), dyt = (double)(P.py - J.ty * kTile);
+    // the quad's 4x4 block: bit 4 (quadrant) + block of the quadrant
+    const uint32_t my_bit = 1u << (8 * (w >> 1) + 4 * (lx >> 3) + 2 * (w & 1) + ((lx >> 2) & 1));
+    const double dxt = (double)lx, dyt = (double)ly;
+    uint8_t* const list = S.list(w);
+    uint32_t* const tri_w = S.tri();
+    uint32_t* const comp_bits = &S.mask[0][0][0];      // with statistics, once the
+    uint32_t* const comp_px = comp_bits + kBatch / 2;  // masks are read: 16 bits per entry
     for (uint32_t b = start; b < end; b += kBatch) {
         const int n = (int)min((uint32_t)kBatch, end - b);
         __syncthreads();
-        if (tid < n) {
-            const uint32_t tri = vals[b + tid];
-            // the statistics' max-weight word; without statistics, the blocks
-            // where the entry composited (one word per entry: no shifts per step)
-            S.tri[tid] = 0u;
-            S.hit[tid] = (uint16_t)stage_rec<true>(S, rec, tri, J.tx * kTile, J.ty * kTile);
+        if ((tid & ~63) < n) {   // the wave stages entries
+            Quads Q{0u, 0u};
+            if (tid < n) {
+                const uint32_t tri = vals[b + tid];
+                // the statistics' max-weight word; without statistics, the blocks
+                // where the entry composited (one word per entry: no shifts per step)
+                tri_w[tid] = 0u;
+                Q = stage_quads(S, rec, tri, J.tx * kTile, J.ty * kTile);
+            }
+            transpose64(Q.lo, Q.hi, lane);
+            S.mask[0][w][lane] = Q.lo;
+            S.mask[1][w][lane] = Q.hi;
         }
-        if (ST && tid < kBatch / 2) S.comp[tid] = 0u;
         __syncthreads();
-        const Lens L = build_lists(S, n, P.w, lane, n, n, n, n);
-        uint32_t* px = reinterpret_cast<uint32_t*>(S.hit);   // 16 bits per entry
-        if constexpr (ST) {   // the hit words are dead once every wave has its lists
+        // lane 4 q + c lists the entries of word c of the wave's quad q
+        const bool word = (lane & 3) * 64 < n;
+        const uint32_t mlo = word ? S.mask[0][lane & 3][16 * w + qi] : 0u;
+        const uint32_t mhi = word ? S.mask[1][lane & 3][16 * w + qi] : 0u;
+        if constexpr (ST) {
             __syncthreads();
-            if (tid < kBatch / 2) px[tid] = 0u;
+            comp_bits[tid] = 0u;
             __syncthreads();
         }
-        // each lane walks its row's list; a row stops once all its pixels are
-        // done, the wave once no row has work left
-        const int len = per_row(P.g, L.n0, L.n1, L.n2, L.n3);
-        const uint8_t* lst = S.list[4 * P.w + P.g];
-        int jn = lst[0];                 // next entry (read one step ahead)
-        bool act = !done && 0 < len;
-        // the test at the bottom keeps the loop a single block (no copies
-        // of the blend state per step)
-        if (__ballot(act) != 0ull) for (int k = 0;;) {
-            // an idle lane reads slot 0 (always staged): a stale slot could hold
-            // non-finite values, and 0 * inf in the branch-free blend is NaN
-            const int jl = jn;              // this step's entry of the row's list
-            const int j = act ? jl : 0;
-            jn = lst[k + 1 < kBatch ? k + 1 : 0];
-            const TriRecord r = read_rec<true>(S, j);
-            Frag f;
-            const bool in = frag_alpha<WIN, false>(r, dxt, dyt, cfg.alpha_max, f);
-            const bool contrib = act && in && f.a >= cfg.alpha_min;
-            const float Tn = T * (1.f - f.a);
-            const bool stop = contrib && Tn < cfg.T_min;
-            const bool comp = contrib && !stop;
-            const float wgt = comp ? f.a * T : 0.f;
-            const float tw = comp ? T * r.o : 0.f;   // blending weight T*o (pruning)
-            if constexpr (FS != 0) {
-                if (comp) {
-                    if constexpr (FS == 2) {
-                        const uint32_t q = foff + fcnt;
-                        J.fentry[q] = b - start + (uint32_t)j;
-                        J.falpha[q] = f.a;
-                        J.fT[q] = T;
+        // all lists at once if they fit, else word by word
+        const int cnt = __popc(mlo) + __popc(mhi);
+        int incl = wave_scan(cnt);
+        const bool fits = __builtin_amdgcn_readlane(incl, 63) <= kWaveList;
+        for (int c = 0; c < (fits ? 1 : kBatch / 64); ++c) {
+            const bool mine = fits || (lane & 3) == c;
+            if (!fits) incl = wave_scan(mine ? cnt : 0);
+            const int excl = incl - (mine ? cnt : 0);
+            {
+                uint32_t ml = mine ? mlo : 0u, mh = mine ? mhi : 0u;
+                int pl = excl, ph = excl + __popc(ml);
+                while (ml | mh) {
+                    if (ml) {
+                        list[pl++] = (uint8_t)((lane & 3) * 64 + __builtin_ctz(ml));
+                        ml &= ml - 1u;
                     }
-                    ++fcnt;
-                }
-            }
-            C0 = fmaf(wgt, r.rgb[0], C0);
-            C1 = fmaf(wgt, r.rgb[1], C1);
-            C2 = fmaf(wgt, r.rgb[2], C2);
-            D = fmaf(wgt, r.z, D);
-            T = comp ? Tn : T;
-            last = comp ? b - start + (uint32_t)j + 1u : last;
-            done = done || stop;
-            if (ST || J.blocks) {
-                const uint64_t cm = __ballot(comp);
-                const uint32_t rowbits = (uint32_t)(cm >> (16 * P.g)) & 0xffffu;
-                if (J.blocks && P.i == 0 && rowbits != 0u) {   // the entry composited in this block
-                    if constexpr (ST) atomicOr(&S.comp[jl >> 1], my_bit << (16 * (jl & 1)));
-                    else atomicOr(&S.tri[jl], my_bit);
-                }
-                if constexpr (ST) {   // pruning statistics of the row's entry, in LDS
-                    const float mw = row_max_f(tw);
-                    if (P.i == 0 && rowbits != 0u) {
-                        atomicMax(&S.tri[jl], __float_as_uint(mw));
-                        atomicAdd(&px[jl >> 1], (uint32_t)__popc(rowbits) << (16 * (jl & 1)));
+                    if (mh) {
+                        list[ph++] = (uint8_t)((lane & 3) * 64 + 32 + __builtin_ctz(mh));
+                        mh &= mh - 1u;
                     }
                 }
             }
-            ++k;
-            act = !done && k < len;
-            if (__ballot(act) == 0ull) break;
+            // the lists are read by other lanes of this wave only: order the byte
+            // writes before those reads without a workgroup barrier
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int from = __builtin_amdgcn_update_dpp(0, excl, 0x00, 0xf, 0xf, true);   // lane 0 of the quad
+            const int len = __builtin_amdgcn_update_dpp(0, incl, 0xFF, 0xf, 0xf, true) - from;   // lane 3
+            // each lane walks its quad's list; a quad stops once all its pixels are
+            // done, the wave once no quad has work left
+            const uint8_t* lst = list + (len > 0 ? from : 0);
+            int jn = lst[0];                 // next entry (read one step ahead)
+            bool act = !done && 0 < len;
+            // the test at the bottom keeps the loop a single block (no copies
+            // of the blend state per step)
+            if (ballot64(act) != 0ull) for (int k = 0;;) {
+                // an idle lane reads slot 0 (always staged): a stale slot could hold
+                // non-finite values, and 0 * inf in the branch-free blend is NaN
+                const int jl = jn;              // this step's entry of the quad's list
+                const int j = act ? jl : 0;
+                jn = lst[k + 1];
+                const TriRecord r = read_rec<true>(S, j);
+                Frag f;
+                const bool in = frag_alpha<WIN, false>(r, dxt, dyt, cfg.alpha_max, f);
+                const bool contrib = act && in && f.a >= cfg.alpha_min;
+                const float Tn = T * (1.f - f.a);
+                const bool stop = contrib && Tn < cfg.T_min;
+                const bool comp = contrib && !stop;
+                const float wgt = comp ? f.a * T : 0.f;
+                const float tw = comp ? T * r.o : 0.f;   // blending weight T*o (pruning)
+                if constexpr (FS != 0) {
+                    if (comp) {
+                        if constexpr (FS == 2) {
+                            const uint32_t q = foff + fcnt;
+                            J.fentry[q] = b - start + (uint32_t)j;
+                            J.falpha[q] = f.a;
+                            J.fT[q] = T;
+                        }
+                        ++fcnt;
+                    }
+                }
+                C0 = fmaf(wgt, r.rgb[0], C0);
+                C1 = fmaf(wgt, r.rgb[1], C1);
+                C2 = fmaf(wgt, r.rgb[2], C2);
+                D = fmaf(wgt, r.z, D);
+                T = comp ? Tn : T;
+                last = comp ? b - start + (uint32_t)j + 1u : last;
+                done = done || stop;
+                if (ST || J.blocks) {
+                    const uint64_t cm = ballot64(comp);
+                    const uint32_t qbits = (uint32_t)(cm >> (lane & ~3)) & 0xfu;
+                    if (J.blocks && i == 0 && qbits != 0u) {   // the entry composited in this block
+                        if constexpr (ST) atomicOr(&comp_bits[jl >> 1], my_bit << (16 * (jl & 1)));
+                        else atomicOr(&tri_w[jl], my_bit);
+                    }
+                    if constexpr (ST) {   // pruning statistics of the quad's entry, in LDS
+                        const float mw = quad_max_f(tw);
+                        if (i == 0 && qbits != 0u) {
+                            atomicMax(&tri_w[jl], __float_as_uint(mw));
+                            atomicAdd(&comp_px[jl >> 1], (uint32_t)__popc(qbits) << (16 * (jl & 1)));
+                        }
+                    }
+                }
+                ++k;
+                act = !done && k < len;
+                if (ballot64(act) == 0ull) break;
+            }
         }
         const bool all_done = __syncthreads_and(done);
         if (J.blocks && tid < n)
-            J.blocks[b + tid] = ST ? (uint16_t)(S.comp[tid >> 1] >> (16 * (tid & 1)))
-                                   : (uint16_t)S.tri[tid];
+            J.blocks[b + tid] = ST ? (uint16_t)(comp_bits[tid >> 1] >> (16 * (tid & 1)))
+                                   : (uint16_t)tri_w[tid];
         if constexpr (ST) {
-            if (tid < n && S.tri[tid] != 0u) {
+            if (tid < n && tri_w[tid] != 0u) {
                 const uint32_t tri = vals[b + tid];
-                atomicMax(reinterpret_cast<uint32_t*>(J.max_weight) + tri, S.tri[tid]);
-                atomicAdd(J.pixels + tri, (px[tid >> 1] >> (16 * (tid & 1))) & 0xffffu);
+                atomicMax(reinterpret_cast<uint32_t*>(J.max_weight) + tri, tri_w[tid]);
+                atomicAdd(J.pixels + tri, (comp_px[tid >> 1] >> (16 * (tid & 1))) & 0xffffu);
             }
         }
         if (all_done) break;
     }
     if (inside) {
-        const int64_t p = (int64_t)P.py * J.W + P.px;
+        const int64_t p = (int64_t)py * J.W + px;
         const int64_t hw = (int64_t)J.W * J.H;
         J.rgb[p] = fmaf(cfg.bg[0], T, C0);
         J.rgb[hw + p] = fmaf(cfg.bg[1], T, C1);
@@ -487,13 +657,13 @@ __global__ __launch_bounds__(256) void k_raster_fwd(
     uint16_t* __restrict__ out_blocks, float* __restrict__ max_weight,
     uint32_t* __restrict__ pixels)
 {
-    __shared__ StageT<WIN, ST> S;
+    __shared__ FwdStage<WIN> S;
     const int tile = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
     if ((unsigned)tile >= (unsigned)num_tiles) return;   // a corrupt order never reads past ranges
     TileJob J{tile % tiles_x, tile / tiles_x, cam.W, cam.H, ranges[2 * tile],
               ranges[2 * tile + 1], out_rgb, out_alpha, out_depth, out_T, out_last, out_blocks,
               max_weight, pixels};
-    fwd_tile(rec, vals, cfg, J, S);
+    fwd_tile<WIN, ST>(rec, vals, cfg, J, S);
 }
 
 // The forward of the stored-fragment variant: FS = 1 counts the composited
@@ -506,7 +676,7 @@ __global__ __launch_bounds__(256) void k_raster_fwd_frag(
     float* __restrict__ out_depth, float* __restrict__ out_T, uint32_t* __restrict__ out_last,
     uint16_t* __restrict__ out_blocks, FragStore fs)
 {
-    __shared__ StageT<WIN, false> S;
+    __shared__ FwdStage<WIN> S;
     const int tile = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
     if ((unsigned)tile >= (unsigned)num_tiles) return;
     TileJob J{tile % tiles_x, tile / tiles_x, cam.W, cam.H, ranges[2 * tile],
@@ -527,12 +697,11 @@ __global__ __launch_bounds__(256) void k_raster_fwd_queue(
     uint32_t* __restrict__ queue, float* __restrict__ out_rgb, float* __restrict__ out_alpha,
     float* __restrict__ out_depth)
 {
-    __shared__ StageT<WIN> S;
-    // the queue slot lives in the stage's block-mask words of the forward
-    // with statistics, which this forward never touches.  A separate
-    // variable would push the workgroup past 25 LDS allocation units (four
-    // per CU, not five).
-    uint32_t& s_t = S.comp[0];
+    __shared__ FwdStage<WIN> S;
+    // the queue slot lives in an entry's word, which is written after the
+    // barrier that follows its reads.  A separate variable would push the
+    // workgroup past 25 LDS allocation units (four per CU, not five).
+    uint32_t& s_t = S.tri()[0];
     const uint32_t nviews = ctl[0], total = ctl[1];
     for (;;) {
         __syncthreads();
@@ -550,7 +719,7 @@ __global__ __launch_bounds__(256) void k_raster_fwd_queue(
         TileJob J{(int)(local % V.tiles_x), (int)(local / V.tiles_x), V.cam.width, V.cam.height,
                   ranges[2 * t], ranges[2 * t + 1], out_rgb + 3 * po, out_alpha + po,
                   out_depth + po, nullptr, nullptr, nullptr, nullptr, nullptr};
-        fwd_tile(rec, vals, cfg, J, S);
+        fwd_tile<WIN, false>(rec, vals, cfg, J, S);
     }
 }
 
@@ -764,7 +933,7 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
                 contrib = j >= 0 && inside && lo_ + (uint32_t)j < my_last && in &&
                           f.a >= cfg.alpha_min;
             }
-            if (__ballot(contrib) == 0ull) continue;
+            if (ballot64(contrib) == 0ull) continue;
 
             const float rom = __builtin_amdgcn_rcpf(1.f - f.a);
             if constexpr (!SF) Ti = T * rom;    // transmittance before this fragment

@@ -13,6 +13,10 @@ constexpr int kTile = TS_TILE;
 constexpr int kBlock = 256;          // threads per tile workgroup (4 wave64)
 constexpr int kWave = 64;
 
+// The lanes of the wave where `b` holds.  On the predicate itself: __ballot
+// takes an int, which costs a select and a compare more per call.
+__device__ __forceinline__ uint64_t ballot64(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+
 // Raster record of one visible triangle, 128 bytes (one L2 line).
 //
 // The window of Eq. (1) is rewritten as three affine functions of the
