@@ -25,6 +25,15 @@
 // lane l shades pixel (l & 3, (l >> 2) & 3) of block g = l >> 4 = (g & 1,
 // g >> 1), and a row sums an entry's gradients over its 16 pixels.
 //
+// Both walks keep their lane masks (active, contributing, composited) as
+// scalars, load a step's record ahead of its arithmetic, and have no branch a
+// wave usually takes.  3M triangles: forward 76.6 -> 73.0 us, backward 153 ->
+// 138 us; 20k at 256x256 22.1 -> 19.5 and 39.1 -> 33.6; sigmoid window 210 -> 198
+// and 480 -> 449.  The backward's sums behind a fragment stay one per channel: a
+// single sum of the scalar products with the upstream gradient is two per cent
+// faster there, and its cancellation cost up to five times the error on vertex
+// gradients (20k triangles, 1e-5 -> 5e-5 of their norm).
+//
 // The window is evaluated as three FP64 affine functions per pixel (gfx950
 // issues v_fma_f64 at the rate of unpacked v_fma_f32); the rest is FP32,
 // written without branches so a wave issues one path per step.  Every
@@ -54,7 +63,7 @@ template <int WIN, int NB>
 struct StageBase : StageExtra<WIN, NB> {
     static constexpr int kN = NB;
     float4 q[kChunks][NB];
-    float z[NB];
+    uint2 zt[NB];            // depth (bits), triangle
     uint16_t hit[NB];        // bit 4 w + g: may composite in block g of quadrant w
     uint8_t list[16][NB];    // per block 4 w + g: its entries of the batch, in order
 };
@@ -77,6 +86,7 @@ struct FwdStage : StageExtra<WIN, kBatch> {
     float4 q[kChunks][kBatch];
     uint32_t mask[2][kBatch / 64][64];
     uint32_t words[kWaveList + kBatch];
+    uint32_t done[4];   // per wave: all its pixels are done
 
     // the lists of wave w; an idle lane may read up to kBatch bytes past their
     // end, in the next wave's lists or the entries' words, and uses nothing of it
@@ -91,11 +101,13 @@ struct FwdStage : StageExtra<WIN, kBatch> {
 // row of global atomics per tile instead of one per 4x4 block: raster backward
 // of 300k triangles (1788 entries per tile) 0.660 -> 0.503 ms.  The other
 // windows' triangles meet 1-2 blocks of a tile, and the LDS sums cost more than
-// the rows saved (3M triangles 0.156 -> 0.193 ms, 20k 0.040 -> 0.055 ms).
+// the rows saved (3M triangles 0.156 -> 0.193 ms, 20k 0.040 -> 0.055 ms).  Pixel
+// quads as the backward's cells, as in the forward: fewer vector instructions
+// (77.0M -> 70.1M at 3M) but 1.5 times the lines of atomics, and slower (0.153
+// -> 0.195 ms, 300k 0.0245 -> 0.0477 ms).
 template <int WIN>
 struct BwdStage : StageBase<WIN, kBatch> {
     static constexpr bool kSums = false;
-    uint32_t tri[1][kBatch];
 };
 template <>
 struct BwdStage<TS_WINDOW_SIGMOID> : StageBase<TS_WINDOW_SIGMOID, 128> {
@@ -132,7 +144,6 @@ __device__ __forceinline__ void write_stage(Stage& S, RecView& u, int tx0, int t
     if constexpr (ZA) u.q[4].z = u.r.z;   // bytes 72-75: the anchor
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) S.q[c][threadIdx.x] = u.q[c];
-    if constexpr (!ZA) S.z[threadIdx.x] = u.r.z;
     if constexpr (Stage::kLse) S.ps[threadIdx.x] = u.r.phis;
 }
 
@@ -146,6 +157,7 @@ __device__ __forceinline__ void stage_copy(Stage& S, const TriRecord* __restrict
 #pragma unroll
     for (int c = 0; c < nc; ++c) u.q[c] = src[c];
     write_stage<ZA>(S, u, tx0, ty0);
+    if constexpr (!ZA) S.zt[threadIdx.x] = make_uint2(__float_as_uint(u.r.z), tri);
 }
 
 template <bool ZA = false, class Stage>
@@ -157,6 +169,7 @@ __device__ __forceinline__ uint32_t stage_rec(Stage& S, const TriRecord* __restr
 #pragma unroll
     for (int c = 0; c < 8; ++c) u.q[c] = src[c];
     write_stage<ZA>(S, u, tx0, ty0);
+    if constexpr (!ZA) S.zt[threadIdx.x] = make_uint2(__float_as_uint(u.r.z), tri);
     uint32_t cx = 0, cy = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -332,7 +345,7 @@ __device__ __forceinline__ TriRecord read_rec(const Stage& S, int j)
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) u.q[c] = S.q[c][j];
     if constexpr (ZA) u.r.z = u.q[4].z;
-    else u.r.z = S.z[j];
+    else u.r.z = __uint_as_float(S.zt[j].x);
     if constexpr (Stage::kLse) u.r.phis = S.ps[j];
     return u.r;
 }
@@ -360,17 +373,17 @@ __device__ __forceinline__ Lens build_lists(Stage& S, int n, int w, int lane, in
         if (c * 64 >= n) break;   // the same for the wave
         const int e = c * 64 + lane;
         const uint32_t h = e < n ? ((uint32_t)S.hit[e] >> (4 * w)) & 0xfu : 0u;
-        auto put = [&](bool bit, uint8_t* lst, int& len) {
-            const uint64_t m = ballot64(bit);
+        auto put = [&](uint32_t bit, int lim, uint8_t* lst, int& len) {
+            const uint64_t m = ballot64(bit != 0u) & ballot64(e < lim);
             const uint32_t below = __builtin_amdgcn_mbcnt_hi(
                 (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            if (bit) lst[len + (int)below] = (uint8_t)e;
+            if (lanes(m)) lst[len + (int)below] = (uint8_t)e;
             len += __popcll(m);
         };
-        put((h & 1u) && e < lim0, l0, L.n0);
-        put((h & 2u) && e < lim1, l1, L.n1);
-        put((h & 4u) && e < lim2, l2, L.n2);
-        put((h & 8u) && e < lim3, l3, L.n3);
+        put(h & 1u, lim0, l0, L.n0);
+        put(h & 2u, lim1, l1, L.n1);
+        put(h & 4u, lim2, l2, L.n2);
+        put(h & 8u, lim3, l3, L.n3);
     }
     // the lists are read by other lanes of this wave only: order the byte
     // writes before those reads without a workgroup barrier
@@ -493,7 +506,7 @@ __device__ __forceinline__ void fwd_tile(const TriRecord* __restrict__ rec,
 
     float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, D = 0.f;
     uint32_t last = 0;
-    bool done = !inside;
+    uint64_t done = ballot64(!inside);   // lanes whose pixel takes nothing more
     uint32_t fcnt = 0, foff = 0;
     if constexpr (FS == 2) {
         if (inside) foff = J.foffs[(int64_t)py * J.W + px];
@@ -506,6 +519,7 @@ __device__ __forceinline__ void fwd_tile(const TriRecord* __restrict__ rec,
     uint32_t* const tri_w = S.tri();
     uint32_t* const comp_bits = &S.mask[0][0][0];      // with statistics, once the
     uint32_t* const comp_px = comp_bits + kBatch / 2;  // masks are read: 16 bits per entry
+    if (lane == 0) S.done[w] = 0u;
     for (uint32_t b = start; b < end; b += kBatch) {
         const int n = (int)min((uint32_t)kBatch, end - b);
         __syncthreads();
@@ -564,23 +578,27 @@ __device__ __forceinline__ void fwd_tile(const TriRecord* __restrict__ rec,
             // each lane walks its quad's list; a quad stops once all its pixels are
             // done, the wave once no quad has work left
             const uint8_t* lst = list + (len > 0 ? from : 0);
-            int jn = lst[0];                 // next entry (read one step ahead)
-            bool act = !done && 0 < len;
-            // the test at the bottom keeps the loop a single block (no copies
-            // of the blend state per step)
-            if (ballot64(act) != 0ull) for (int k = 0;;) {
+            int jn = lst[0];   // next entry (read one step ahead)
+            asm volatile("" : "+v"(jn));   // else kept as a byte and widened every step
+            // Lane masks are scalars (a ballot of a comparison is the comparison),
+            // so a step's conditions and the marks below cost no vector
+            // instruction.  The test at the bottom keeps the loop a single block
+            // (no copies of the blend state per step).
+            uint64_t act = ballot64(0 < len) & ~done;
+            if (act != 0ull) for (int k = 0;;) {
                 // an idle lane reads slot 0 (always staged): a stale slot could hold
                 // non-finite values, and 0 * inf in the branch-free blend is NaN
                 const int jl = jn;              // this step's entry of the quad's list
-                const int j = act ? jl : 0;
+                const int j = lanes(act) ? jl : 0;
                 jn = lst[k + 1];
                 const TriRecord r = read_rec<true>(S, j);
                 Frag f;
                 const bool in = frag_alpha<WIN, false>(r, dxt, dyt, cfg.alpha_max, f);
-                const bool contrib = act && in && f.a >= cfg.alpha_min;
+                const uint64_t contrib = act & ballot64(in) & ballot64(f.a >= cfg.alpha_min);
                 const float Tn = T * (1.f - f.a);
-                const bool stop = contrib && Tn < cfg.T_min;
-                const bool comp = contrib && !stop;
+                const uint64_t stop = contrib & ballot64(Tn < cfg.T_min);
+                const uint64_t composited = contrib & ~stop;
+                const bool comp = lanes(composited);
                 const float wgt = comp ? f.a * T : 0.f;
                 const float tw = comp ? T * r.o : 0.f;   // blending weight T*o (pruning)
                 if constexpr (FS != 0) {
@@ -600,28 +618,30 @@ __device__ __forceinline__ void fwd_tile(const TriRecord* __restrict__ rec,
                 D = fmaf(wgt, r.z, D);
                 T = comp ? Tn : T;
                 last = comp ? b - start + (uint32_t)j + 1u : last;
-                done = done || stop;
+                done |= stop;
                 if (ST || J.blocks) {
-                    const uint64_t cm = ballot64(comp);
-                    const uint32_t qbits = (uint32_t)(cm >> (lane & ~3)) & 0xfu;
-                    if (J.blocks && i == 0 && qbits != 0u) {   // the entry composited in this block
+                    uint64_t any = composited | (composited >> 1);   // lane 0 of each quad
+                    any = (any | (any >> 2)) & 0x1111111111111111ull;
+                    if (J.blocks && lanes(any)) {   // the entry composited in this block
                         if constexpr (ST) atomicOr(&comp_bits[jl >> 1], my_bit << (16 * (jl & 1)));
                         else atomicOr(&tri_w[jl], my_bit);
                     }
                     if constexpr (ST) {   // pruning statistics of the quad's entry, in LDS
                         const float mw = quad_max_f(tw);
-                        if (i == 0 && qbits != 0u) {
+                        if (lanes(any)) {
+                            const uint32_t qbits = (uint32_t)(composited >> (lane & ~3)) & 0xfu;
                             atomicMax(&tri_w[jl], __float_as_uint(mw));
                             atomicAdd(&comp_px[jl >> 1], (uint32_t)__popc(qbits) << (16 * (jl & 1)));
                         }
                     }
                 }
                 ++k;
-                act = !done && k < len;
-                if (ballot64(act) == 0ull) break;
+                act = ballot64(k < len) & ~done;
+                if (act == 0ull) break;
             }
         }
-        const bool all_done = __syncthreads_and(done);
+        if (done == ~0ull && lane == 0) S.done[w] = 1u;
+        __syncthreads();
         if (J.blocks && tid < n)
             J.blocks[b + tid] = ST ? (uint16_t)(comp_bits[tid >> 1] >> (16 * (tid & 1)))
                                    : (uint16_t)tri_w[tid];
@@ -632,7 +652,7 @@ __device__ __forceinline__ void fwd_tile(const TriRecord* __restrict__ rec,
                 atomicAdd(J.pixels + tri, (comp_px[tid >> 1] >> (16 * (tid & 1))) & 0xffffu);
             }
         }
-        if (all_done) break;
+        if ((S.done[0] & S.done[1] & S.done[2] & S.done[3]) != 0u) break;
     }
     if (inside) {
         const int64_t p = (int64_t)py * J.W + px;
@@ -886,7 +906,7 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
         }
         if (tid < n) {
             const uint32_t tri = vals[start + lo_ + tid];
-            S.tri[par][tid] = tri;
+            if constexpr (SUMS) S.tri[par][tid] = tri;
             if (blocks) {   // the forward's record of where the entry composited
                 stage_copy(S, rec, tri, tx * kTile, ty * kTile);
                 S.hit[tid] = blocks[start + lo_ + tid];
@@ -898,26 +918,34 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
         // entries of this batch each row needs (before its last composited one)
         const Lens L = build_lists(S, n, P.w, lane, rl0 - (int)lo_, rl1 - (int)lo_,
                                    rl2 - (int)lo_, rl3 - (int)lo_);
-        const int len = per_row(P.g, L.n0, L.n1, L.n2, L.n3);
-        const int steps = max(max(L.n0, L.n1), max(L.n2, L.n3));
-        const uint8_t* lst = S.list[4 * P.w + P.g];
-        int kn = len - 1;
-        int jn = lst[kn >= 0 ? kn : 0];   // next entry (read one step ahead)
-        for (int st = 0; st < steps; ++st) {   // back to front along each row's list
-            const int k = kn;
-            const int jc = k >= 0 ? jn : 0;   // idle lanes read slot 0 (always staged)
-            --kn;
-            jn = lst[kn >= 0 ? kn : 0];
-            const int j = k >= 0 ? jc : -1;
+        // back to front along each row's list; positions are bytes from the start
+        // of the stage, and a row past its list's front reads bytes before it
+        // that it does not use
+        const uint8_t* const bytes = reinterpret_cast<const uint8_t*>(&S);
+        const int front = (int)(&S.list[4 * P.w + P.g][0] - bytes);
+        int at = front + per_row(P.g, L.n0, L.n1, L.n2, L.n3) - 1;
+        int jn = bytes[at];   // next entry (read one step ahead)
+        asm volatile("" : "+v"(jn));   // else kept as a byte and widened every step
+        const int lim = (int)my_last - (int)lo_;   // entries of the batch the pixel needs
+        for (;;) {
+            // lane masks are scalars, as in the forward
+            const uint64_t act = ballot64(at >= front);
+            if (act == 0ull) break;
+            const int jc = lanes(act) ? jn : 0;   // idle lanes read slot 0 (always staged)
+            jn = bytes[--at];
             const TriRecord r = read_rec(S, jc);
+            const uint32_t tri = S.zt[jc].y;
+            // the loads stay ahead of the arithmetic and of the branch below, so a
+            // step waits for LDS once
+            asm volatile("" ::: "memory");
             const int dx = P.px - r.ax, dy = P.py - r.ay;   // anchor form of the coefficients
             Frag f;
             const bool in = frag_alpha<WIN>(r, dxt, dyt, cfg.alpha_max, f);
-            bool contrib;
+            uint64_t contribs;
             float Ti;
             if constexpr (SF) {
-                contrib = j >= 0 && fcur >= flo && fe == lo_ + (uint32_t)j;
-                if (contrib) {
+                contribs = act & ballot64(fcur >= flo) & ballot64(fe == lo_ + (uint32_t)jc);
+                if (lanes(contribs)) {
                     f.a = fa;
                     Ti = fTb;
                     --fcur;
@@ -930,14 +958,24 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
                     }
                 }
             } else {
-                contrib = j >= 0 && inside && lo_ + (uint32_t)j < my_last && in &&
-                          f.a >= cfg.alpha_min;
+                // my_last is 0 outside the image
+                contribs = act & ballot64(jc < lim) & ballot64(in) &
+                           ballot64(f.a >= cfg.alpha_min);
             }
-            if (ballot64(contrib) == 0ull) continue;
+            if (contribs == 0ull) continue;
 
-            const float rom = __builtin_amdgcn_rcpf(1.f - f.a);
-            if constexpr (!SF) Ti = T * rom;    // transmittance before this fragment
-            const float wgt = contrib ? f.a * Ti : 0.f;
+            const bool contrib = lanes(contribs);
+            float rom, wgt;   // 1 / (1 - a), a T
+            if constexpr (SF) {
+                rom = __builtin_amdgcn_rcpf(1.f - f.a);
+                wgt = contrib ? f.a * Ti : 0.f;
+            } else {
+                const float a = contrib ? f.a : 0.f;
+                rom = __builtin_amdgcn_rcpf(1.f - a);   // 1 / 1 = 1: T stays
+                T *= rom;
+                Ti = T;   // transmittance before this fragment
+                wgt = a * Ti;
+            }
             float v[16];
             v[11] = g0 * wgt;
             v[12] = g1 * wgt;
@@ -951,8 +989,7 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
             S1 = fmaf(wgt, r.rgb[1], S1);
             S2 = fmaf(wgt, r.rgb[2], S2);
             SD = fmaf(wgt, r.z, SD);
-            T = contrib ? Ti : T;
-            const bool open = contrib && f.oI <= cfg.alpha_max;   // not clamped
+            const bool open = lanes(contribs & ballot64(f.oI <= cfg.alpha_max));   // not clamped
             const float gI = ga * r.o;
             v[9] = open ? ga * f.I : 0.f;                                  // dL/do
             if constexpr (WIN == TS_WINDOW_LSE) {
@@ -980,25 +1017,27 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
                     v[10] = open ? -gI * dI * f.u * rs : 0.f;
                     gu = open ? gI * dI : 0.f;
                 } else {
-                    v[10] = open ? gI * f.I * (f.lg * 0.69314718055994531f) : 0.f;  // I ln u
-                    gu = open ? gI * r.sigma * f.I * __builtin_amdgcn_rcpf(f.u) : 0.f;
+                    // computed for all lanes and selected: no branch in the step
+                    const float vs = gI * f.I * (f.lg * 0.69314718055994531f);  // I ln u
+                    const float vu = gI * r.sigma * f.I * __builtin_amdgcn_rcpf(f.u);
+                    v[10] = open ? vs : 0.f;
+                    gu = open ? vu : 0.f;
                 }
-                const float a_ = gu * (float)dx, b_ = gu * (float)dy;
-                v[0] = f.k == 0 ? a_ : 0.f;
-                v[1] = f.k == 1 ? a_ : 0.f;
-                v[2] = f.k == 2 ? a_ : 0.f;
-                v[3] = f.k == 0 ? b_ : 0.f;
-                v[4] = f.k == 1 ? b_ : 0.f;
-                v[5] = f.k == 2 ? b_ : 0.f;
-                v[6] = f.k == 0 ? gu : 0.f;
-                v[7] = f.k == 1 ? gu : 0.f;
-                v[8] = f.k == 2 ? gu : 0.f;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const float gk = f.k == q ? gu : 0.f;
+                    v[q] = gk * (float)dx;
+                    v[3 + q] = gk * (float)dy;
+                    v[6 + q] = gk;
+                }
             }
             const float tot = row_reduce16(v, P.i);
             // slot 15 carries dL/dr for the LogSumExp window only
-            if (j >= 0 && P.i < (WIN == TS_WINDOW_LSE ? 16 : 15) && tot != 0.f) {
+            constexpr uint64_t slots =
+                WIN == TS_WINDOW_LSE ? ~0ull : 0x7fff7fff7fff7fffull;
+            if (lanes(act & slots & ballot64(tot != 0.f))) {
                 if constexpr (SUMS) unsafeAtomicAdd(&S.acc[jc * TS_G2D_STRIDE + P.i], tot);
-                else unsafeAtomicAdd(g2d + (int64_t)S.tri[0][jc] * TS_G2D_STRIDE + P.i, tot);
+                else unsafeAtomicAdd(g2d + (int64_t)tri * TS_G2D_STRIDE + P.i, tot);
             }
         }
         hi_ = lo_;

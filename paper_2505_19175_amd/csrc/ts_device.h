@@ -17,6 +17,10 @@ constexpr int kWave = 64;
 // takes an int, which costs a select and a compare more per call.
 __device__ __forceinline__ uint64_t ballot64(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 
+// Whether this lane is in a (wave-uniform) lane mask: no instruction, the mask
+// is the condition.
+__device__ __forceinline__ bool lanes(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
 // Raster record of one visible triangle, 128 bytes (one L2 line).
 //
 // The window of Eq. (1) is rewritten as three affine functions of the
