@@ -374,8 +374,8 @@ size_t ts_batch_workspace_bytes(int64_t N, int32_t max_views, uint64_t capacity,
  *   - one projection pass loads every triangle once and sets it up for all
  *     views of the batch (record of (view, triangle) at view * N + triangle)
  *   - one binning pass orders the instances of all views by batch-wide tile
- *   - one persistent launch drains a tile queue shared by the views, so
- *     views of different resolutions balance across the chip.
+ *   - one launch walks the tiles of all views, longest first, so views of
+ *     different resolutions balance across the chip.
  * Arguments (device unless noted):
  *   views      [max_views] views, laid out by ts_batch_layout
  *   ctl        [2] uint32: number of views in this batch, their total tiles

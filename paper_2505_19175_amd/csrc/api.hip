@@ -511,22 +511,10 @@ int ts_render_forward_batched(const float* v, const float* o, const float* sigma
         return fail(TS_EWORKSPACE, "ts_render_forward_batched: workspace too small");
     const ts::BinWorkspace w = ts::carve_bin_workspace(ws, entries, bins->capacity, (int64_t)max_tiles);
     uint32_t* extra = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(ws) + need.bytes);
-    uint32_t* queue = extra;        // tile queue head
     uint32_t* bctl = extra + 4;     // clamped descriptor: views, tiles, views * N
     uint32_t* n_entries = bctl + 2;
     const ts::Cfg g = to_cfg(cfg);
 
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            cus <= 0)
-            cus = 256;
-    }
-    const int workgroups = (int)std::min<int64_t>((int64_t)max_tiles, (int64_t)cus * 4);
-
-    ts::launch_fill_u32(queue, 1, 0u, stream);
     ts::launch_batch_ctl(ctl, (uint32_t)max_views, max_tiles, N, bctl, stream);
     ts::launch_project_views(v, o, sigma, sh, N, views, bctl, g, proj->rec, proj->rect,
                              proj->depth, proj->ntiles, stream);
@@ -535,9 +523,8 @@ int ts_render_forward_batched(const float* v, const float* o, const float* sigma
                                     views, N, 0, (int)max_tiles, w, *bins, nullptr, &overflow,
                                     stream, bctl + 1);
     if (e != hipSuccess) return hip_fail(e, "ts_render_forward_batched");
-    ts::launch_raster_forward_queue(proj->rec, bins->vals, bins->ranges, bins->order, views, bctl,
-                                    g, queue,
-                                    workgroups, rgb, alpha, depth, stream);
+    ts::launch_raster_forward_views(proj->rec, bins->vals, bins->ranges, bins->order, views, bctl,
+                                    g, max_tiles, rgb, alpha, depth, stream);
     e = hipGetLastError();
     return e == hipSuccess ? TS_OK : hip_fail(e, "ts_render_forward_batched");
 }

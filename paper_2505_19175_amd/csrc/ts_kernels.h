@@ -129,11 +129,10 @@ void launch_backproject_adam(float* v, float* a, float* b, float* sh, float* o, 
 // views[i] += pixels[i] > 1; pixels[i] = 0.
 void launch_prune_views(uint32_t* pixels, uint32_t* views, int64_t N, hipStream_t stream);
 
-void launch_raster_forward_queue(const void* rec, const uint32_t* vals, const uint32_t* ranges,
+void launch_raster_forward_views(const void* rec, const uint32_t* vals, const uint32_t* ranges,
                                  const uint32_t* order, const ts_view* views,
-                                 const uint32_t* ctl, const Cfg& cfg,
-                                 uint32_t* queue, int workgroups, float* rgb, float* alpha,
-                                 float* depth, hipStream_t stream);
+                                 const uint32_t* ctl, const Cfg& cfg, uint32_t max_tiles,
+                                 float* rgb, float* alpha, float* depth, hipStream_t stream);
 
 // Stored-fragment variant (the memory form the recompute backward is
 // measured against): per pixel the number of composited fragments and the
