@@ -522,13 +522,14 @@ __device__ __forceinline__ void fwd_tile(const TriRecord* __restrict__ rec,
     uint32_t* const comp_bits = &S.mask[0][0][0];      // with statistics, once the
     uint32_t* const comp_px = comp_bits + kBatch / 2;  // masks are read: 16 bits per entry
     if (lane == 0) S.done[w] = 0u;
+    uint32_t next = start + tid < end ? vals[start + tid] : 0u;   // entry to stage, loaded a batch ahead
     for (uint32_t b = start; b < end; b += kBatch) {
         const int n = (int)min((uint32_t)kBatch, end - b);
         __syncthreads();
         if ((tid & ~63) < n) {   // the wave stages entries
             Quads Q{0u, 0u};
             if (tid < n) {
-                const uint32_t tri = vals[b + tid];
+                const uint32_t tri = next;
                 // the statistics' max-weight word; without statistics, the blocks
                 // where the entry composited (one word per entry: no shifts per step)
                 tri_w[tid] = 0u;
@@ -538,6 +539,7 @@ __device__ __forceinline__ void fwd_tile(const TriRecord* __restrict__ rec,
             S.mask[0][w][lane] = Q.lo;
             S.mask[1][w][lane] = Q.hi;
         }
+        next = b + kBatch + tid < end ? vals[b + kBatch + tid] : 0u;
         __syncthreads();
         // lane 4 q + c lists the entries of word c of the wave's quad q
         const bool word = (lane & 3) * 64 < n;
@@ -897,6 +899,9 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
     if constexpr (SUMS)
         for (int f = tid; f < NB * TS_G2D_STRIDE; f += kBlock) S.acc[f] = 0.f;
     int last_n = 0, par = 0;
+    // entry to stage, loaded a batch ahead
+    const uint32_t lo0 = jmax > (uint32_t)NB ? jmax - NB : 0u;
+    uint32_t next = tid < (int)(jmax - lo0) ? vals[start + lo0 + tid] : 0u;
     for (uint32_t hi_ = jmax; hi_ > 0;) {
         const uint32_t lo_ = hi_ > (uint32_t)NB ? hi_ - NB : 0u;
         const int n = (int)(hi_ - lo_);
@@ -907,7 +912,7 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
             par ^= 1;
         }
         if (tid < n) {
-            const uint32_t tri = vals[start + lo_ + tid];
+            const uint32_t tri = next;
             if constexpr (SUMS) S.tri[par][tid] = tri;
             if (blocks) {   // the forward's record of where the entry composited
                 stage_copy(S, rec, tri, tx * kTile, ty * kTile);
@@ -915,6 +920,10 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
             } else {
                 S.hit[tid] = (uint16_t)stage_rec(S, rec, tri, tx * kTile, ty * kTile);
             }
+        }
+        {
+            const uint32_t lo1 = lo_ > (uint32_t)NB ? lo_ - NB : 0u;
+            next = tid < (int)(lo_ - lo1) ? vals[start + lo1 + tid] : 0u;
         }
         __syncthreads();
         // entries of this batch each row needs (before its last composited one)
