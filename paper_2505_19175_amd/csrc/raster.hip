@@ -97,6 +97,11 @@ struct FwdStage : StageExtra<WIN, kBatch> {
     __device__ uint32_t* tri() { return words + kWaveList; }
 };
 
+constexpr int kWideImage = 1024;         // fewest tiles of an image that has wide entries summed
+constexpr int kWideSlots = 10;            // what 25 LDS allocation units leave room for
+constexpr int kWideBlocks = 8;            // blocks of the tile that make an entry wide
+constexpr uint32_t kWideTri = 0xffffff00u;   // above any triangle: a slot, not a triangle
+
 // The backward's LDS.  Sigmoid window: its triangles cover most blocks of many
 // tiles, so the entries' 2D gradients are summed over the tile's blocks here
 // (batches of 128 entries: the sums take 64 bytes each) and an entry costs one
@@ -107,12 +112,28 @@ struct FwdStage : StageExtra<WIN, kBatch> {
 // quads as the backward's cells, as in the forward: fewer vector instructions
 // (77.0M -> 70.1M at 3M) but 1.5 times the lines of atomics, and slower (0.153
 // -> 0.195 ms, 300k 0.0245 -> 0.0477 ms).
-template <int WIN>
+//
+// Wide entries (W): where a few triangles cover many tiles, their lines take an
+// atomic per block from all over the chip, one after another.  In a batch the
+// first kWideSlots entries that composited in half a tile's blocks are summed
+// here and cost one row per tile; their zt holds the slot instead of the
+// triangle.  Raster backward of a 300k-triangle cluster view with such
+// triangles 63.9 -> 22 us; a step pays one comparison more (3M triangles 137.1
+// -> 139.1 us, 20k at 256x256 34.6 -> 35.5), so small images, where no triangle
+// covers many tiles, go without.
+template <int WIN, bool W>
 struct BwdStage : StageBase<WIN, kBatch> {
     static constexpr bool kSums = false;
 };
+template <int WIN>
+struct BwdStage<WIN, true> : StageBase<WIN, kBatch> {
+    static constexpr bool kSums = false;
+    uint32_t wide[2];              // wide entries of this batch and of the one before
+    uint32_t tri[2][kWideSlots];   // their triangles
+    float acc[kWideSlots * TS_G2D_STRIDE];
+};
 template <>
-struct BwdStage<TS_WINDOW_SIGMOID> : StageBase<TS_WINDOW_SIGMOID, 128> {
+struct BwdStage<TS_WINDOW_SIGMOID, false> : StageBase<TS_WINDOW_SIGMOID, 128> {
     static constexpr bool kSums = true;
     uint32_t tri[2][128];   // of this batch and of the one whose sums are written
     float acc[128 * TS_G2D_STRIDE];
@@ -813,7 +834,7 @@ __device__ __forceinline__ uint32_t row_max(uint32_t x)
 // SF: the stored-fragment variant: the composited fragments of each pixel,
 // their alphas and transmittances come from the forward's store (fs) instead
 // of the recomputed cut-off decisions and T_before = T_after / (1 - alpha).
-template <int WIN, bool SF = false>
+template <int WIN, bool SF = false, bool WIDE = false>
 __global__ __launch_bounds__(256) void k_raster_bwd(
     const TriRecord* __restrict__ rec, const uint32_t* __restrict__ vals,
     const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ order, Cam cam, Cfg cfg,
@@ -822,7 +843,7 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
     const float* __restrict__ T_final, const uint32_t* __restrict__ last_in,
     const uint16_t* __restrict__ blocks, float* __restrict__ g2d, FragStore fs)
 {
-    __shared__ BwdStage<WIN> S;
+    __shared__ BwdStage<WIN, WIDE> S;
     __shared__ uint32_t s_max;
     const int tile = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
     if ((unsigned)tile >= (unsigned)num_tiles) return;   // a corrupt order never reads past ranges
@@ -881,11 +902,11 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
     __syncthreads();
     const uint32_t jmax = s_max;   // entries any pixel of the tile needs
 
-    constexpr bool SUMS = BwdStage<WIN>::kSums;
-    constexpr int NB = BwdStage<WIN>::kN;
+    constexpr bool SUMS = BwdStage<WIN, WIDE>::kSums;
+    constexpr int NB = BwdStage<WIN, WIDE>::kN;
     // a batch's sums -> the triangles' accumulators, and zeros again
     auto flush = [&](int n, int b) {
-        if constexpr (SUMS) {
+        if constexpr (SUMS || WIDE) {
             for (int f = tid; f < n * TS_G2D_STRIDE; f += kBlock) {
                 const float x = S.acc[f];
                 if (x != 0.f) {
@@ -896,8 +917,12 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
             }
         }
     };
-    if constexpr (SUMS)
-        for (int f = tid; f < NB * TS_G2D_STRIDE; f += kBlock) S.acc[f] = 0.f;
+    if constexpr (SUMS || WIDE)
+        for (int f = tid; f < (SUMS ? NB : kWideSlots) * TS_G2D_STRIDE; f += kBlock)
+            S.acc[f] = 0.f;
+    if constexpr (WIDE) {
+        if (tid < 2) S.wide[tid] = 0u;
+    }
     int last_n = 0, par = 0;
     // entry to stage, loaded a batch ahead
     const uint32_t lo0 = jmax > (uint32_t)NB ? jmax - NB : 0u;
@@ -909,8 +934,11 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
         if constexpr (SUMS) {
             flush(last_n, par);
             last_n = n;
-            par ^= 1;
         }
+        if constexpr (WIDE) {
+            flush((int)min(S.wide[par], (uint32_t)kWideSlots), par);
+        }
+        par ^= 1;
         if (tid < n) {
             const uint32_t tri = next;
             if constexpr (SUMS) S.tri[par][tid] = tri;
@@ -920,12 +948,24 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
             } else {
                 S.hit[tid] = (uint16_t)stage_rec(S, rec, tri, tx * kTile, ty * kTile);
             }
+            if constexpr (WIDE) {
+                if (__popc(S.hit[tid]) >= kWideBlocks) {
+                    const uint32_t slot = atomicAdd(&S.wide[par], 1u);
+                    if (slot < (uint32_t)kWideSlots) {
+                        S.tri[par][slot] = tri;
+                        S.zt[tid].y = kWideTri + slot;
+                    }
+                }
+            }
         }
         {
             const uint32_t lo1 = lo_ > (uint32_t)NB ? lo_ - NB : 0u;
             next = tid < (int)(lo_ - lo1) ? vals[start + lo1 + tid] : 0u;
         }
         __syncthreads();
+        if constexpr (WIDE) {
+            if (tid == 0) S.wide[par ^ 1] = 0u;   // its batch was written before the barrier
+        }
         // entries of this batch each row needs (before its last composited one)
         const Lens L = build_lists(S, n, P.w, lane, rl0 - (int)lo_, rl1 - (int)lo_,
                                    rl2 - (int)lo_, rl3 - (int)lo_);
@@ -1047,15 +1087,24 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
             constexpr uint64_t slots =
                 WIN == TS_WINDOW_LSE ? ~0ull : 0x7fff7fff7fff7fffull;
             if (lanes(act & slots & ballot64(tot != 0.f))) {
-                if constexpr (SUMS) unsafeAtomicAdd(&S.acc[jc * TS_G2D_STRIDE + P.i], tot);
-                else unsafeAtomicAdd(g2d + (int64_t)tri * TS_G2D_STRIDE + P.i, tot);
+                if constexpr (SUMS) {
+                    unsafeAtomicAdd(&S.acc[jc * TS_G2D_STRIDE + P.i], tot);
+                } else {
+                    if (WIDE && tri >= kWideTri) {
+                        if constexpr (WIDE)
+                            unsafeAtomicAdd(&S.acc[(tri - kWideTri) * TS_G2D_STRIDE + P.i], tot);
+                    } else {
+                        unsafeAtomicAdd(g2d + (int64_t)tri * TS_G2D_STRIDE + P.i, tot);
+                    }
+                }
             }
         }
         hi_ = lo_;
     }
-    if constexpr (SUMS) {
+    if constexpr (SUMS || WIDE) {
         __syncthreads();
-        flush(last_n, par);
+        if constexpr (SUMS) flush(last_n, par);
+        else flush((int)min(S.wide[par], (uint32_t)kWideSlots), par);
     }
 }
 
@@ -1144,7 +1193,10 @@ void launch_raster_backward(const void* rec, const uint32_t* vals, const uint32_
     switch (cfg.window) {
     case TS_WINDOW_SIGMOID: go(k_raster_bwd<TS_WINDOW_SIGMOID>); break;
     case TS_WINDOW_LSE: go(k_raster_bwd<TS_WINDOW_LSE>); break;
-    default: go(k_raster_bwd<TS_WINDOW_PAPER>); break;
+    default:
+        if (num_tiles >= kWideImage) go(k_raster_bwd<TS_WINDOW_PAPER, false, true>);
+        else go(k_raster_bwd<TS_WINDOW_PAPER>);
+        break;
     }
 }
 
