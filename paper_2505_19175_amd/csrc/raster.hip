@@ -118,9 +118,10 @@ constexpr uint32_t kWideTri = 0xffffff00u;   // above any triangle: a slot, not 
 // first kWideSlots entries that composited in half a tile's blocks are summed
 // here and cost one row per tile; their zt holds the slot instead of the
 // triangle.  Raster backward of a 300k-triangle cluster view with such
-// triangles 63.9 -> 22 us; a step pays one comparison more (3M triangles 137.1
-// -> 139.1 us, 20k at 256x256 34.6 -> 35.5), so small images, where no triangle
-// covers many tiles, go without.
+// triangles 63.9 -> 22 us; the LogSumExp step of four 300k soups 119-136 ->
+// 107-115 us.  A step pays one comparison more (3M triangles 137.1 -> 139.1 us,
+// 20k at 256x256 34.6 -> 35.5), so small images, where no triangle covers many
+// tiles, go without.
 template <int WIN, bool W>
 struct BwdStage : StageBase<WIN, kBatch> {
     static constexpr bool kSums = false;
@@ -1192,7 +1193,10 @@ void launch_raster_backward(const void* rec, const uint32_t* vals, const uint32_
     }
     switch (cfg.window) {
     case TS_WINDOW_SIGMOID: go(k_raster_bwd<TS_WINDOW_SIGMOID>); break;
-    case TS_WINDOW_LSE: go(k_raster_bwd<TS_WINDOW_LSE>); break;
+    case TS_WINDOW_LSE:
+        if (num_tiles >= kWideImage) go(k_raster_bwd<TS_WINDOW_LSE, false, true>);
+        else go(k_raster_bwd<TS_WINDOW_LSE>);
+        break;
     default:
         if (num_tiles >= kWideImage) go(k_raster_bwd<TS_WINDOW_PAPER, false, true>);
         else go(k_raster_bwd<TS_WINDOW_PAPER>);

@@ -36,8 +36,9 @@ def test_quad_lists(window, n, size, W, H):
 
 # Triangles that cover many of an image's tiles, up to and beyond the entries
 # of a batch that the backward sums per tile, and over several batches.
+@pytest.mark.parametrize("window", [WINDOW_PAPER, WINDOW_LSE])
 @pytest.mark.parametrize("n", [1, 10, 11, 300])
-def test_wide_entries(n):
+def test_wide_entries(n, window):
     wide, cam = random_soup(61, n, W=520, H=512, size=1.5, deg=1, sigma=(0.3, 2.0), o=(0.02, 0.1),
                             dtype=np.float32)
     small, _ = random_soup(62, 200, W=520, H=512, size=0.05, deg=1, sigma=(0.3, 2.0), o=(0.2, 0.9),
@@ -45,7 +46,7 @@ def test_wide_entries(n):
     sc = type(wide)(*(np.concatenate([a, b]) for a, b in
                       zip((wide.v, wide.o, wide.sigma, wide.sh),
                           (small.v, small.o, small.sigma, small.sh))))
-    cfg = Config(sh_degree=1, bg=(0.1, 0.2, 0.3), window=WINDOW_PAPER)
+    cfg = Config(sh_degree=1, bg=(0.1, 0.2, 0.3), window=window)
     ras, st, sct, out = G.gpu_forward(sc, cam, cfg, capacity=1 << 20)
     ref = O.render(sc, cam, cfg)
     G.assert_forward(G.to_np(out), ref, resolve=(sc, cam, cfg, True))
