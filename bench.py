@@ -40,13 +40,13 @@ TRAFFIC = {
     "project_bwd": {"files": ["paper_2505_19175_amd/csrc/backproject.hip",
                               "paper_2505_19175_amd/csrc/geometry.h",
                               "paper_2505_19175_amd/csrc/ts_device.h"],
-                    "src": "2f75c1b29f27ca26ded13886dbdef84017ac581d79288b4e0be0c2219d11aea2",
+                    "src": "cd6fa70cd90c6bd24183b5b358c63bae077cb5e234b05634044a53f10cc690c8",
                     "fetch_kib": 1.615e5, "write_kib": 7.807e5,
                     "fetch_scale": 2.0, "write_scale": 1.0},
     "project": {"files": ["paper_2505_19175_amd/csrc/project.hip",
                           "paper_2505_19175_amd/csrc/geometry.h",
                           "paper_2505_19175_amd/csrc/ts_device.h"],
-                "src": "ff00d4a2a94574088ef47d699290f7606ccaf8e6ec59cef61445af4cc2573524",
+                "src": "bea379f629b3a5884f3924460b988e9c306ff526f9da5bbbf21d628849b4d886",
                 "fetch_kib": 2.148e5, "write_kib": 3.104e5,
                 "fetch_scale": 2.0, "write_scale": 1.0},
 }
