@@ -46,7 +46,7 @@
 namespace ts {
 
 constexpr int kBatch = kBlock;   // entries staged per batch
-constexpr int kChunks = 6;       // 16-byte chunks of a record the raster reads (+ z)
+constexpr int kChunks = 6;       // 16-byte chunks of a record the raster reads (and its depth)
 
 // phi_lse(s) of each staged entry, for the LogSumExp window only: the other
 // windows get an empty base, so their LDS footprint (32000 bytes, 25 blocks
@@ -99,7 +99,7 @@ struct FwdStage : StageExtra<WIN, kBatch> {
 
 constexpr int kWideImage = 1024;         // fewest tiles of an image that has wide entries summed
 constexpr int kWideSlots = 10;            // what 25 LDS allocation units leave room for
-constexpr int kWideBlocks = 8;            // blocks of the tile that make an entry wide
+constexpr int kWideBlocks = 8;            // blocks of the tile that make an entry wide (4, 6: +1 us at 3M)
 constexpr uint32_t kWideTri = 0xffffff00u;   // above any triangle: a slot, not a triangle
 
 // The backward's LDS.  Sigmoid window: its triangles cover most blocks of many
