@@ -1017,17 +1017,12 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
             if (contribs == 0ull) continue;
 
             const bool contrib = lanes(contribs);
-            float rom, wgt;   // 1 / (1 - a), a T
-            if constexpr (SF) {
-                rom = __builtin_amdgcn_rcpf(1.f - f.a);
-                wgt = contrib ? f.a * Ti : 0.f;
-            } else {
-                const float a = contrib ? f.a : 0.f;
-                rom = __builtin_amdgcn_rcpf(1.f - a);   // 1 / 1 = 1: T stays
-                T *= rom;
-                Ti = T;   // transmittance before this fragment
-                wgt = a * Ti;
-            }
+            const float rom = __builtin_amdgcn_rcpf(1.f - f.a);
+            if constexpr (!SF) Ti = T * rom;   // transmittance before this fragment
+            // selected, not a product with a zero alpha: behind an alpha of one
+            // (T_min = 0) T is NaN, and lanes that composite nothing add zero
+            const float wgt = contrib ? f.a * Ti : 0.f;
+            if constexpr (!SF) T = contrib ? Ti : T;
             float v[16];
             v[11] = g0 * wgt;
             v[12] = g1 * wgt;

@@ -55,3 +55,42 @@ def test_wide_entries(n, window):
     dC, dA, dD = dC * keep[None], dA * keep, dD * keep
     g = G.gpu_backward(ras, st, sct, out, dC, dA, dD)
     G.assert_grads(g, O.backward(sc, cam, cfg, dC, dA, dD))
+
+
+@pytest.mark.parametrize("window,sigma", [(WINDOW_PAPER, 1.0), (WINDOW_SIGMOID, 0.05),
+                                          (WINDOW_LSE, 1.0)])
+@pytest.mark.parametrize("W,H", [(16, 16), (528, 512)])   # the second sums wide entries
+def test_opaque_neighbour_leaves_gradients_alone(window, sigma, W, H):
+    """An opaque triangle (alpha 1, T_min 0: its own gradient is undefined)
+    behind one that shares its 4x4 block of pixels but none of its pixels: the
+    second one's gradients are those it has alone."""
+    f = 16.0
+
+    def tri(pts, z):
+        return [[(x - W / 2) * z / f, (y - H / 2) * z / f, z] for x, y in pts]
+
+    v = np.array([tri([(-6, -6), (2.2, -6), (-2, 30)], 4.0),
+                  tri([(2.2, -40), (14, -40), (2.4, 60)], 2.0)], np.float32)
+    o = np.array([1.0, 0.5], np.float32)
+    s = np.array([1e-12, sigma], np.float32)
+    sh = np.array([[[0.3, 0.2, 0.1]], [[0.5, 0.1, 0.4]]], np.float32)
+    both = synth.Scene(v, o, s, sh)
+    alone = synth.Scene(*(a[1:] for a in (v, o, s, sh)))
+    cam = synth.Camera(np.eye(3, dtype=np.float32), np.zeros(3, np.float32), f, f, W / 2, H / 2,
+                       W, H).astype32()
+    cfg = Config(sh_degree=0, alpha_max=1.0, T_min=0.0, window=window)
+    dC, dA, dD = synth.upstream(3, W, H, True, True)
+    ras, st, sct, out = G.gpu_forward(both, cam, cfg)
+    opaque = out.T_final.cpu().numpy() == 0.0
+    assert opaque.any()
+    g = G.gpu_backward(ras, st, sct, out, dC, dA, dD)
+    ras, st, sct, out = G.gpu_forward(alone, cam, cfg)
+    # no pixel of the two in common, some 4x4 block in common
+    mine = out.last.cpu().numpy() > 0
+    assert mine.any() and not (mine & opaque).any()
+    blocks = lambda m: m[:H // 4 * 4, :W // 4 * 4].reshape(H // 4, 4, W // 4, 4).any((1, 3))
+    assert (blocks(mine) & blocks(opaque)).any()
+    a = G.gpu_backward(ras, st, sct, out, dC, dA, dD)
+    for k in g:   # the same FP32 terms, summed in another order
+        np.testing.assert_allclose(g[k][1], a[k][0], rtol=0,
+                                   atol=G.GRAD_RTOL * np.abs(a[k]).max())
