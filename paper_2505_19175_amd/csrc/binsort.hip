@@ -36,6 +36,7 @@
 // addresses.  No kernel waits on another block, so nothing can spin.
 // Element counts are read from device memory, so the whole chain can run
 // without a host round trip (grids sized by upper bounds).
+#include "tile_starts.h"
 #include "ts_device.h"
 #include "ts_kernels.h"
 
@@ -816,44 +817,42 @@ __device__ __forceinline__ uint32_t group_sum(uint32_t v, uint32_t* s_tmp)
 }
 
 // Exclusive scan of s_t[0 .. T) in LDS by the workgroup, T <= kGroupTiles; each
-// thread owns a slice of consecutive tiles.  Returns the total.
+// thread owns a slice of consecutive tiles.  Returns the total; it and the starts
+// saturate (tile_starts.h).
 constexpr int kTileSlice = kGroupTiles / kGroupThreads;
 static_assert(kTileSlice * kGroupThreads == kGroupTiles, "whole slices");
 
-__device__ __forceinline__ uint64_t scan_tiles(uint32_t* s_t, int T, uint32_t* s_tmp)
+__device__ __forceinline__ uint32_t scan_tiles(uint32_t* s_t, int T, uint32_t* s_tmp)
 {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int per = (T + kGroupThreads - 1) / kGroupThreads, t0 = tid * per;
-    uint32_t s = 0;
-    for (int r = 0; r < per; ++r) s += t0 + r < T ? s_t[t0 + r] : 0u;
-    uint32_t inc = s;
+    const int per = (T + kGroupThreads - 1) / kGroupThreads;
+    const int t0 = min(T, tid * per), t1 = min(T, t0 + per);
+    const uint32_t s = slice_sum(s_t, t0, t1);
+    // the slices before the thread's own (a saturated sum has no inverse, so the
+    // sums are shifted by a lane first)
+    uint32_t pre = __shfl_up(s, 1, 64);
+    if (lane == 0) pre = 0u;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(inc, d, 64);
-        if (lane >= d) inc += y;
+        const uint32_t y = __shfl_up(pre, d, 64);
+        if (lane >= d) pre = add_sat(pre, y);
     }
-    if (lane == 63) s_tmp[w] = inc;
+    if (lane == 63) s_tmp[w] = add_sat(pre, s);
     __syncthreads();
-    uint32_t start = inc - s;
-    uint64_t M = 0;
+    uint32_t start = 0, M = 0;   // of the wave; of all
     for (int j = 0; j < kGroupThreads / 64; ++j) {
-        start += j < w ? s_tmp[j] : 0u;
-        M += s_tmp[j];
+        if (j == w) start = M;
+        M = add_sat(M, s_tmp[j]);
     }
-    for (int r = 0; r < per; ++r) {
-        if (t0 + r < T) {
-            const uint32_t c = s_t[t0 + r];
-            s_t[t0 + r] = start;
-            start += c;
-        }
-    }
+    start = add_sat(start, pre);
+    slice_starts(s_t, t0, t1, start);
     __syncthreads();
     return M;
 }
 
 // Where the binning writes what it found.
 struct GroupOut {
-    uint64_t capacity;
+    uint32_t capacity;   // below 2^32 - kGroupThreads (list_capacity)
     uint32_t* ranges;
     uint32_t* order;
     uint32_t* n_long;
@@ -864,28 +863,26 @@ struct GroupOut {
     uint32_t* d_Nv;
 };
 
-__device__ __forceinline__ void write_totals(uint64_t M, const GroupOut& o)
+__device__ __forceinline__ void write_totals(uint32_t M, const GroupOut& o)
 {
-    *o.d_M = (uint32_t)min(M, (uint64_t)0xffffffffu);
-    *o.d_sortn = (uint32_t)min(M, o.capacity);
+    *o.d_M = M;
+    *o.d_sortn = min(M, o.capacity);
     *o.d_ovf = M > o.capacity ? 1u : 0u;
 }
 
 // From the starts s_t[0 .. T) and the total M: the ranges (clamped to the
 // capacity; an empty tile's range is (0, 0)) and the longest-first order of
 // the first n tiles.
-__device__ __forceinline__ void write_ranges(const uint32_t* s_t, int T, int n, uint64_t M,
+__device__ __forceinline__ void write_ranges(const uint32_t* s_t, int T, int n, uint32_t M,
                                              const GroupOut& o, OrderSmem& sm)
 {
     auto bounds = [&](int t) {
-        const uint64_t a = s_t[t], b = t + 1 < T ? (uint64_t)s_t[t + 1] : M;
-        return make_uint2((uint32_t)min(a, o.capacity), (uint32_t)min(b, o.capacity));
+        return clamp_run(s_t[t], t + 1 < T ? s_t[t + 1] : M, o.capacity);
     };
     uint2* r2 = reinterpret_cast<uint2*>(o.ranges);
     const bool pair = (reinterpret_cast<uintptr_t>(o.ranges) & 7u) == 0u;
     for (int t = threadIdx.x; t < T; t += kGroupThreads) {
-        uint2 r = bounds(t);
-        if (r.x == r.y) r = make_uint2(0u, 0u);
+        const uint2 r = bounds(t);
         if (pair) {
             r2[t] = r;
         } else {
@@ -900,11 +897,23 @@ __device__ __forceinline__ void write_ranges(const uint32_t* s_t, int T, int n, 
 
 static_assert(kOrderThreads == kGroupThreads, "the order is made by a placing workgroup");
 
-// Puts an instance at slot p of the list, unless it is past the capacity (as
-// the clamped ranges say).
-__device__ __forceinline__ uint32_t cap32(uint64_t capacity)
+// The capacity the grouping works with: a workgroup's threads may each move a
+// cursor past it once (put), and no cursor wraps.
+static uint32_t list_capacity(uint64_t capacity)
 {
-    return capacity < 0xffffffffull ? (uint32_t)capacity : 0xffffffffu;
+    constexpr uint64_t most = 0xffffffffull - kGroupThreads;
+    return (uint32_t)(capacity < most ? capacity : most);
+}
+
+// Puts instance id of a tile at the tile's cursor, unless that is past the
+// capacity (as the clamped ranges say).  `full`: the list does not hold all
+// instances, and a cursor that has reached the capacity stays there.
+__device__ __forceinline__ void put(uint32_t* cursor, uint32_t id, uint32_t capacity, bool full,
+                                    uint32_t* __restrict__ vals)
+{
+    if (full && *reinterpret_cast<volatile uint32_t*>(cursor) >= capacity) return;
+    const uint32_t p = atomicAdd(cursor, 1u);
+    if (p < capacity) vals[p] = id;
 }
 
 // One workgroup bins everything (N <= kOneEntries entries of one view, T <=
@@ -935,21 +944,17 @@ __global__ __launch_bounds__(kGroupThreads) void k_bin_one(
         });
     }
     vis = group_sum(vis, s_tmp);   // a barrier inside: the counts are whole
-    const uint64_t M = scan_tiles(s_t, T, s_tmp2);
+    const uint32_t M = scan_tiles(s_t, T, s_tmp2);
     if (tid == 0) {
         write_totals(M, o);
         *o.d_Nv = vis;
     }
     write_ranges(s_t, T, d_tiles ? (int)min(*d_tiles, (uint32_t)T) : T, M, o, sm);
     __syncthreads();
-    const uint32_t cap = cap32(o.capacity);
 #pragma unroll
     for (int k = 0; k < kRounds; ++k)
         for_run_tiles<1>(k * kGroupThreads + tid, u[k], vt, [&](uint32_t t, uint32_t id) {
-            if (t < (uint32_t)T) {
-                const uint32_t p = atomicAdd(&s_t[t], 1u);
-                if (p < cap) vals[p] = id;
-            }
+            if (t < (uint32_t)T) put(&s_t[t], id, o.capacity, false, vals);   // far below 2^32
         });
 }
 
@@ -1090,7 +1095,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(
         s_t[t] = all;
     }
     __syncthreads();
-    const uint64_t M = scan_tiles(s_t, T, s_tmp);
+    const uint32_t M = scan_tiles(s_t, T, s_tmp);
     if (head) {
         const uint32_t vis = sum_groups(grp, G, s_tmp2);
         if (tid == 0) {
@@ -1103,21 +1108,18 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(
 #pragma unroll
     for (int k = 0; k < kTileSlice; ++k) {
         const int t = k * kGroupThreads + tid;
-        if (t < T) s_t[t] += before[k];
+        if (t < T) s_t[t] = first_slot(s_t[t], before[k], o.capacity);
     }
     __syncthreads();
-    const uint32_t cap = cap32(o.capacity);
+    const bool full = M > o.capacity;
     for_group_tiles<R>(G, g, ntiles, rect, tg, [&](uint32_t t, uint32_t id) {
-        if (t < (uint32_t)T) {
-            const uint32_t p = atomicAdd(&s_t[t], 1u);
-            if (p < cap) vals[p] = id;
-        }
+        if (t < (uint32_t)T) put(&s_t[t], id, o.capacity, full, vals);
     });
 }
 
 // More tiles than a workgroup's 32-bit counters: one workgroup scans the
 // totals of the batch's tiles (*d_tiles of the T budgeted) in chunks into the
-// ranges, and writes the totals.  start[t] receives the unclamped starts.
+// ranges, and writes the totals.  start[t] receives the starts.
 __global__ __launch_bounds__(kGroupThreads) void k_group_ranges_wide(
     const uint32_t* __restrict__ tot, int T, const uint32_t* __restrict__ d_tiles,
     const uint32_t* __restrict__ grp, int G, GroupOut o, uint32_t* __restrict__ start)
@@ -1127,7 +1129,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_ranges_wide(
     __shared__ uint32_t s_tmp[kGroupThreads / 64], s_tmp2[kGroupThreads / 64];
     const int tid = threadIdx.x;
     const int n = d_tiles ? (int)min(*d_tiles, (uint32_t)T) : T;
-    uint64_t M = 0;
+    uint32_t M = 0;
     for (int t0 = 0; t0 < n; t0 += kPart) {
         const int m = min(kPart, n - t0);
 #pragma unroll
@@ -1136,17 +1138,17 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_ranges_wide(
             if (t < m) s_t[t] = tot[t0 + t];
         }
         __syncthreads();
-        const uint64_t sum = scan_tiles(s_t, m, s_tmp);
+        const uint32_t sum = scan_tiles(s_t, m, s_tmp);
         for (int t = tid; t < m; t += kGroupThreads) {
-            const uint64_t a = M + s_t[t], b = M + (t + 1 < m ? (uint64_t)s_t[t + 1] : sum);
-            const uint32_t ra = (uint32_t)min(a, o.capacity), rb = (uint32_t)min(b, o.capacity);
-            start[t0 + t] = (uint32_t)a;
-            if (ra != rb) {   // the counting launch cleared the ranges
-                o.ranges[2 * (t0 + t)] = ra;
-                o.ranges[2 * (t0 + t) + 1] = rb;
+            const uint32_t a = add_sat(M, s_t[t]), b = add_sat(M, t + 1 < m ? s_t[t + 1] : sum);
+            const uint2 r = clamp_run(a, b, o.capacity);
+            start[t0 + t] = a;
+            if (r.x != r.y) {   // the counting launch cleared the ranges
+                o.ranges[2 * (t0 + t)] = r.x;
+                o.ranges[2 * (t0 + t) + 1] = r.y;
             }
         }
-        M += sum;
+        M = add_sat(M, sum);
         __syncthreads();   // the chunk is read by its neighbours' threads
     }
     const uint32_t vis = sum_groups(grp, G, s_tmp2);
@@ -1176,18 +1178,16 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place_wide(
     }
     const int g = xcd_group((int)blockIdx.x - 1, G);
     const uint32_t* row = hist + (int64_t)g * T;
-    const uint32_t cap = cap32(o.capacity);
+    const bool full = *o.d_ovf != 0u;
     for (int w0 = 0; w0 < Ta; w0 += kWideTiles) {
         const int m = min(kWideTiles, Ta - w0);
         __syncthreads();
-        for (int t = tid; t < m; t += kGroupThreads) s_t[t] = start[w0 + t] + row[w0 + t];
+        for (int t = tid; t < m; t += kGroupThreads)
+            s_t[t] = first_slot(start[w0 + t], row[w0 + t], o.capacity);
         __syncthreads();
         for_group_tiles<R>(G, g, ntiles, rect, tg, [&](uint32_t t, uint32_t id) {
             const uint32_t tw = t - (uint32_t)w0;
-            if (tw < (uint32_t)m) {
-                const uint32_t p = atomicAdd(&s_t[tw], 1u);
-                if (p < cap) vals[p] = id;
-            }
+            if (tw < (uint32_t)m) put(&s_t[tw], id, o.capacity, full, vals);
         });
     }
 }
@@ -2007,7 +2007,7 @@ hipError_t run_bin_sort(const uint32_t* ntiles, const float* depth, const int16_
         // 1'. grouping by group tile counts
         const uint2* r4 = reinterpret_cast<const uint2*>(rect);
         const TileGrid tg{views, per_view, tiles_x, N, d_n};
-        const GroupOut go{out.capacity, out.ranges, order, n_long, out.d_count + 3,
+        const GroupOut go{list_capacity(out.capacity), out.ranges, order, n_long, out.d_count + 3,
                           d_M, d_sortn, d_ovf, d_Nv};
         const int64_t want = (N + kGroupEntries - 1) / kGroupEntries;
         const int G = want < 1 ? 1 : want > kMaxGroups ? kMaxGroups : (int)want;
@@ -2058,7 +2058,7 @@ hipError_t run_bin_sort(const uint32_t* ntiles, const float* depth, const int16_
         if (err != hipSuccess) return err;
         err = hipStreamSynchronize(stream);
         if (err != hipSuccess) return err;
-        *overflow = (uint64_t)h_count[0] > out.capacity;
+        *overflow = h_count[0] > go.capacity;
         return hipSuccess;
     }
 

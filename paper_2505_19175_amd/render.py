@@ -102,6 +102,13 @@ class ViewState:
                               self.capacity, self._state.ptr("order"), ls.ptr("blocks"),
                               B.TS_BINS_SEGMENTED_SORT if self.segmented else 0)
 
+    def _grow(self, M: int):
+        """Lists for a view of M instances, which the present ones do not hold."""
+        if M > 0xffffffff - 1024:   # the count saturates; the binning keeps 1024 slots free
+            raise B.TSError(B.TS_ECAPACITY, "ViewState",
+                            "the view has more instances than a list can hold")
+        self._alloc_lists(min(int(M * 1.25) + 1024, 0xffffffff))
+
     def __getattr__(self, name):
         # a buffer's tensor (rec, rect, vals, ranges, ...), kept once made
         for part in ("_state", "_lists"):
@@ -165,7 +172,7 @@ class Rasterizer:
             except B.TSError as e:
                 if e.code != B.TS_ECAPACITY:
                     raise
-                st._alloc_lists(int(st.count[0] * 1.25) + 1024)
+                st._grow(int(st.count[0]))
                 continue
             break
         if sync:
@@ -220,7 +227,7 @@ class Rasterizer:
                 st.M, st.N_v = M, N_v
                 self._seen_huge(st, huge)
                 return out
-            st._alloc_lists(int(M * 1.25) + 1024)
+            st._grow(M)
 
     def backward(self, st: ViewState, scene_t, out: Outputs, dC, dA=None, dD=None, grads=None):
         v, o, sigma, sh = scene_t

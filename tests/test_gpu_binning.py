@@ -142,3 +142,77 @@ def test_batch_windows_equal_single_views(n, sizes, budget):
             for a, b in ((rgb, out.rgb), (alpha, out.alpha), (depth, out.depth)):
                 assert torch.equal(a, b)
         assert res.instances == total
+
+
+def _disjoint_runs(ranges, cap):
+    r = ranges[ranges[:, 1] != ranges[:, 0]]
+    r = r[np.argsort(r[:, 0])]
+    assert (r[:, 0] < r[:, 1]).all() and r[0, 0] == 0 and r[-1, 1] == cap
+    assert (r[1:, 0] == r[:-1, 1]).all()
+
+
+# More than 2^32 instances: 2^21 boxes over all of 3600 tiles (in 32 bits every
+# 2048th tile starts at 0), 1.25M over 3600.
+@pytest.mark.parametrize("N", [1 << 21, 1_250_000])
+@pytest.mark.parametrize("cap", [5000, 3_000_000])
+def test_more_instances_than_32_bits(N, cap):
+    W, H = 1280, 720
+    rect = np.tile(np.array([0, W - 1, 0, H - 1], np.int16), (N, 1))
+    nt = np.full(N, 3600, np.int32)
+    depth = (np.random.default_rng(N).permutation(N) + 1).astype(np.float32)
+    st, _ = _bin(rect, nt, depth, W, H, cap, sync=False)
+    d = st.d_count.cpu().numpy().view(np.uint32)
+    assert d[0] == 0xffffffff and d[1] == N and d[2] == 1
+    r, got = st.ranges.cpu().numpy(), st.vals.cpu().numpy()
+    _disjoint_runs(r, cap)
+    for t in np.flatnonzero(r[:, 1] > r[:, 0]):
+        run = got[r[t, 0]:r[t, 1]]
+        assert (run >= 0).all() and (run < N).all() and len(set(run.tolist())) == len(run)
+        assert (np.diff(depth[run]) > 0).all()
+
+
+def _covering(n):
+    """Triangles over the whole image of an identity camera."""
+    rng = np.random.Generator(np.random.PCG64(n))
+    z = rng.uniform(3.0, 4.0, n).astype(np.float32)
+    v = np.empty((n, 3, 3), np.float32)
+    v[:, :, :2] = np.array([[-400, -300], [400, -300], [0, 500]], np.float32)
+    v[:, :, 2] = z[:, None]
+    sh = rng.uniform(-1.0, 1.0, (n, 1, 3)).astype(np.float32)
+    return synth.Scene(v, np.full(n, 0.3, np.float32), np.ones(n, np.float32), sh)
+
+
+def test_view_of_more_instances_than_a_list_holds_is_refused():
+    """The view is refused with the capacity error, before lists are allocated
+    for what the 32-bit count says."""
+    n, W, H = 540_000, 1920, 1080
+    scene = scene_to_device(_covering(n), DEV)
+    cfg = synth.Config(sh_degree=0)
+    st, ras = ViewState(n, W, H, 4096), Rasterizer(cfg)
+    cam = synth.identity_camera(W, H)
+    for call in (lambda: ras.forward(st, scene, cam, sync=True),
+                 lambda: ras.bin_sort(st, ras.project(st, scene, cam))):
+        with pytest.raises(B.TSError) as e:
+            call()
+        assert e.value.code == B.TS_ECAPACITY
+    assert st.capacity == 4096
+    few = scene_to_device(_covering(20), DEV)   # each covers every tile
+    st = ViewState(20, W, H, 4096)
+    ras.forward(st, few, cam, sync=True)
+    assert st.M == 20 * st.num_tiles
+
+
+def test_batch_of_more_instances_than_32_bits():
+    n, W, H, cap = 70_000, 1920, 1080, 100_000
+    scene = scene_to_device(_covering(n), DEV)
+    cam = synth.identity_camera(W, H)
+    ex = BatchedExecutor(scene, synth.Config(sh_degree=0), time.perf_counter, max_views=8,
+                         max_tiles=8 * 8160, max_pixels=8 * W * H, capacity=cap, slots=1)
+    batch = [Request(i, cam, 0.0) for i in range(8)]
+    ex.submit(0, batch)
+    while (res := ex.poll(0)) is None:
+        pass
+    assert res.overflow and ex._slots[0].count_host.numpy().view(np.uint32)[0] == 0xffffffff
+    _disjoint_runs(ex._slots[0].ranges.cpu().numpy(), cap)
+    for rgb, alpha, depth in ex.outputs(0, batch):
+        assert all(bool(torch.isfinite(x).all()) for x in (rgb, alpha, depth))
