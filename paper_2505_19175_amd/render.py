@@ -227,6 +227,8 @@ class Rasterizer:
                 st.M, st.N_v = M, N_v
                 self._seen_huge(st, huge)
                 return out
+            # the render reads the lists, and this stream need not be theirs
+            torch.cuda.current_stream().synchronize()
             st._grow(M)
 
     def backward(self, st: ViewState, scene_t, out: Outputs, dC, dA=None, dD=None, grads=None):

@@ -216,3 +216,27 @@ def test_batch_of_more_instances_than_32_bits():
     _disjoint_runs(ex._slots[0].ranges.cpu().numpy(), cap)
     for rgb, alpha, depth in ex.outputs(0, batch):
         assert all(bool(torch.isfinite(x).all()) for x in (rgb, alpha, depth))
+
+
+def test_short_lists_on_another_stream():
+    """A state whose lists are too short, rendered on a stream other than the one
+    its buffers come from, while that one allocates blocks of the lists' size."""
+    n, W, H = 200_000, 1280, 720
+    rng = np.random.Generator(np.random.PCG64(8))
+    scene = scene_to_device(synth.cluster_soup(8, n, sh_degree=0, edge_median=0.1, rng=rng), DEV)
+    cfg = synth.Config(sh_degree=0)
+    cam = synth.look_at(synth.hemisphere_eyes(rng, 1)[0], width=W, height=H)
+    ref = ViewState(n, W, H, 1 << 22, device=DEV)
+    want = Rasterizer(cfg).forward(ref, scene, cam, sync=True)
+    side = torch.cuda.Stream()
+    for cap in (1, 1000, ref.M - 1, ref.M):
+        st = ViewState(n, W, H, cap, device=DEV)
+        size = st._lists.raw.numel()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            out = Rasterizer(cfg).forward(st, scene, cam, sync=True)
+        junk = [torch.full((size,), 255, dtype=torch.uint8, device=DEV) for _ in range(4)]
+        torch.cuda.synchronize()
+        assert st.M == ref.M and st.capacity >= ref.M and len(junk) == 4
+        for a, b in ((out.rgb, want.rgb), (out.alpha, want.alpha), (out.depth, want.depth)):
+            assert torch.equal(a, b)
