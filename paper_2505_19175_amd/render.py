@@ -84,23 +84,29 @@ class ViewState:
         self.N_v = None
 
     def _alloc_lists(self, capacity: int):
-        self.capacity = int(max(capacity, 1))
+        capacity = int(max(capacity, 1))
         for name in ("vals", "keys", "blocks", "ws"):
             self.__dict__.pop(name, None)
-        self.ws_bytes = B.ts_bin_sort_workspace_bytes(self.N, self.capacity, self.num_tiles)
-        specs = [("vals", (self.capacity,), torch.int32), ("blocks", (self.capacity,), torch.int16),
-                 ("ws", (self.ws_bytes,), torch.uint8)]
-        if self.want_keys:
-            specs.append(("keys", (self.capacity,), torch.int64))
-        else:
+        if not self.want_keys:
             self.keys = None
-        self._lists = None   # the old lists go before the new ones come
+        # the old lists go before the new ones come; should that allocation fail,
+        # the library refuses the null pointers and the next call allocates again
+        self._lists, self.bins, self.ws_ptr, self.ws_bytes = None, B.ts_bins(), None, 0
+        ws_bytes = B.ts_bin_sort_workspace_bytes(self.N, capacity, self.num_tiles)
+        specs = [("vals", (capacity,), torch.int32), ("blocks", (capacity,), torch.int16),
+                 ("ws", (ws_bytes,), torch.uint8)]
+        if self.want_keys:
+            specs.append(("keys", (capacity,), torch.int64))
         ls = self._lists = _Arena(self.device, specs)
-        self.ws_ptr = ls.ptr("ws")
+        self.capacity, self.ws_ptr, self.ws_bytes = capacity, ls.ptr("ws"), ws_bytes
         self.bins = B.ts_bins(ls.ptr("keys") if self.want_keys else None, ls.ptr("vals"),
                               self._state.ptr("ranges"), self._state.ptr("d_count"),
                               self.capacity, self._state.ptr("order"), ls.ptr("blocks"),
                               B.TS_BINS_SEGMENTED_SORT if self.segmented else 0)
+
+    def _need_lists(self):
+        if self._lists is None:
+            self._alloc_lists(self.capacity)
 
     def _grow(self, M: int):
         """Lists for a view of M instances, which the present ones do not hold."""
@@ -165,6 +171,7 @@ class Rasterizer:
 
     def bin_sort(self, st: ViewState, ccam, sync: bool = True):
         """With sync, read back (M, N_v) and grow the lists until they fit."""
+        st._need_lists()
         while True:
             try:
                 B.ts_bin_sort(st.proj, st.N, ccam, st.ws_ptr, st.ws_bytes, st.bins,
@@ -202,6 +209,7 @@ class Rasterizer:
             B.ts_prune_count_views(stats.pixels, stats.views, st.N, stream)
             return out
         late = sync and not st.segmented
+        st._need_lists()
         while True:
             if late:
                 # the counts' copy is waited for after the render is enqueued,

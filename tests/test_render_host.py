@@ -92,3 +92,24 @@ def test_lists_are_freed_after_the_render_that_reads_them(monkeypatch):
     assert first[-1] == "wait stream" and first.index("render") < len(first) - 1
     assert host.log[len(first) + 1:] == ["bin", "event", "render", "wait event"]
     assert (st.M, st.N_v) == (400, 9) and st.capacity >= 400
+
+
+@pytest.mark.parametrize("sync", [True, False])
+def test_failed_growth_leaves_no_pointer_to_freed_lists(monkeypatch, sync):
+    """Out of memory while the lists grow: the state holds null pointers (which
+    the library refuses) until the next call has allocated its lists again."""
+    st, host, forward = _view(monkeypatch, 100, [(400, 9, 0), (70, 9, 0)])
+    arena = render._Arena
+
+    def fail(*a):
+        raise torch.OutOfMemoryError("out of memory")
+
+    monkeypatch.setattr(render, "_Arena", fail)
+    with pytest.raises(torch.OutOfMemoryError):
+        forward()
+    assert st.bins.vals is None and st.bins.blocks is None and st.bins.capacity == 0
+    assert st.ws_ptr is None and st.ws_bytes == 0 and not hasattr(st, "vals")
+    monkeypatch.setattr(render, "_Arena", arena)
+    forward(sync=sync)
+    assert st.capacity == st.bins.capacity == 100 and st.vals.numel() == 100
+    assert st.bins.vals == st.vals.data_ptr() and st.ws_ptr == st.ws.data_ptr()
