@@ -49,7 +49,8 @@ def _deliver(frames, d2h: bool):
         return out
     src = [t for f in frames for t in f]
     dst = [torch.empty_like(t) for t in src]
-    torch._foreach_copy_(dst, src)
+    if src:   # an empty batch is accepted, an empty list of tensors is not
+        torch._foreach_copy_(dst, src)
     return [tuple(dst[i:i + 3]) for i in range(0, len(dst), 3)]
 
 

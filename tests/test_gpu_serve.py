@@ -178,3 +178,18 @@ def test_continuous_batching_delivers_every_frame(soup, d2h):
         if not d2h:
             np.testing.assert_array_equal(got[i][1], ref[1])
             np.testing.assert_array_equal(got[i][2], ref[2])
+
+
+@pytest.mark.parametrize("d2h", [False, True])
+def test_empty_batch_is_accepted(soup, d2h):
+    """A batch of no requests completes, and the slot takes the next one."""
+    sc, cfg, st = soup
+    cam = _cams(7, [(320, 200)])[0]
+    ex = BatchedExecutor(st, cfg, time.perf_counter, max_views=2, max_tiles=2 * 260,
+                         max_pixels=2 * 320 * 200, capacity=1 << 20, slots=1, d2h=d2h)
+    for batch in ([], [Request(0, cam, 0.0)], []):
+        ex.submit(0, batch)
+        res = _wait(ex, 0)
+        assert not res.overflow and (res.instances > 0) == bool(batch)
+        for r in batch:
+            np.testing.assert_array_equal(r.result[0].cpu().numpy(), _alone(st, cfg, cam)[0])

@@ -137,3 +137,18 @@ def test_batching_beats_one_view_per_launch_at_saturation():
 def test_tiles_of():
     assert tiles_of(1920, 1080) == 120 * 68
     assert tiles_of(640, 360) == 40 * 23
+
+
+@pytest.mark.parametrize("frames", [0, 1, 3])
+def test_delivered_frames_are_copies(frames):
+    """Each frame's tensors copied, for a batch of any size down to none."""
+    torch = pytest.importorskip("torch")
+    from paper_2505_19175_amd.serve.executor import _deliver
+    src = [(torch.randn(3, 4 + i, 5), torch.randn(4 + i, 5), torch.randn(4 + i, 5))
+           for i in range(frames)]
+    got = _deliver(src, False)
+    assert len(got) == frames
+    for f, g in zip(src, got):
+        for a, b in zip(f, g):
+            assert torch.equal(a, b) and a.data_ptr() != b.data_ptr()
+    assert _deliver([], True) == []
