@@ -208,9 +208,9 @@ class Rasterizer:
                                       out.depth, out.T_final, out.last, stats.c, stream)
             B.ts_prune_count_views(stats.pixels, stats.views, st.N, stream)
             return out
-        late = sync and not st.segmented
         st._need_lists()
         while True:
+            late = sync and not st.segmented
             if late:
                 # the counts' copy is waited for after the render is enqueued,
                 # so the GPU does not wait for the host in between; lists that
@@ -237,6 +237,7 @@ class Rasterizer:
                 return out
             # the render reads the lists, and this stream need not be theirs
             torch.cuda.current_stream().synchronize()
+            self._seen_huge(st, huge)   # clamped runs: at least as long in the new lists
             st._grow(M)
 
     def backward(self, st: ViewState, scene_t, out: Outputs, dC, dA=None, dD=None, grads=None):

@@ -553,3 +553,14 @@ def test_raster_backward_twice_without_projection_is_rejected(small):
     torch.cuda.synchronize()
     G.assert_grads({k: g.cpu().numpy().astype(np.float64) for k, g in zip(("v", "o", "sigma", "sh"), grads)},
                    {k: g.cpu().numpy().astype(np.float64) for k, g in zip(("v", "o", "sigma", "sh"), first)})
+
+
+def test_short_lists_and_a_huge_tile():
+    """A first view whose lists are too short and one of whose tiles holds more
+    than 4096 entries even in them: grown and sorted over many workgroups in the
+    same call, bit-exact against the oracle's stable sort."""
+    sc, cam = _one_tile_soup(64, 9000, "ulps")
+    cfg = Config(sh_degree=0)
+    ras, st, sct, out = G.gpu_forward(sc, cam, cfg, capacity=5000)
+    assert st.segmented and st.capacity >= 9000 and int(st.d_count[3].item()) == 1
+    _check_bins(st, sc, cam, cfg)

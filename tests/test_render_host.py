@@ -113,3 +113,12 @@ def test_failed_growth_leaves_no_pointer_to_freed_lists(monkeypatch, sync):
     forward(sync=sync)
     assert st.capacity == st.bins.capacity == 100 and st.vals.numel() == 100
     assert st.bins.vals == st.vals.data_ptr() and st.ws_ptr == st.ws.data_ptr()
+
+
+def test_huge_tiles_seen_in_short_lists(monkeypatch):
+    """Lists too short and a tile already beyond one workgroup's sort in them:
+    the repeated binning sorts such tiles over many workgroups."""
+    st, host, forward = _view(monkeypatch, 5000, [(9000, 9, 1)])
+    forward()
+    assert host.flags == [0, B.TS_BINS_SEGMENTED_SORT]
+    assert st.segmented and st.bins.flags == B.TS_BINS_SEGMENTED_SORT and st.M == 9000
