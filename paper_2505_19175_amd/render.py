@@ -184,7 +184,8 @@ class Rasterizer:
             break
         if sync:
             st.M, st.N_v = int(st.count[0]), int(st.count[1])
-            self._seen_huge(st, int(st.d_count[3].item()))
+            if not st.segmented:   # one more read of the device
+                self._seen_huge(st, int(st.d_count[3].item()))
 
     @staticmethod
     def _seen_huge(st: ViewState, huge: int):

@@ -122,3 +122,24 @@ def test_huge_tiles_seen_in_short_lists(monkeypatch):
     forward()
     assert host.flags == [0, B.TS_BINS_SEGMENTED_SORT]
     assert st.segmented and st.bins.flags == B.TS_BINS_SEGMENTED_SORT and st.M == 9000
+
+
+def test_segmented_view_reads_the_counts_once(monkeypatch):
+    """A state that sorts its huge tiles segment-wise has nothing to learn from
+    their count: the binning's own read is the only one."""
+    st, host, forward = _view(monkeypatch, 5000, [(4500, 9, 1)])
+    forward()
+    assert st.segmented
+    counts = st.d_count
+
+    class Counts:
+        def copy_(self, t):
+            counts.copy_(t)
+
+        def __getitem__(self, i):
+            raise AssertionError("read back")
+
+    monkeypatch.setattr(st, "d_count", Counts())
+    host.log.clear()
+    forward()
+    assert host.log == ["bin", "render"] and st.M == 4500
