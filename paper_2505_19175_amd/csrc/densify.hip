@@ -18,6 +18,12 @@ constexpr int kPickChunk = 4 * kDensBlock;   // triangles per workgroup of the s
 // after another on an idle chip).
 constexpr int kMany = 8, kFew = 2;
 constexpr int64_t kFewTriangles = 1 << 18;
+// From these sizes on, the sums that every workgroup would repeat get a launch of
+// their own, since both the workgroups and the sums grow with the soup.  Selection,
+// repeated / own launch: 2M 12.4 / 13.7 us, 4M 20.3 / 20.2, 8M 37.8 / 31.9, 100M
+// 1260 / 292.  Subdivision (sums over spans of the chunk counts): 1M 34.6 / 37.0,
+// 2M 53.9 / 54.8, 3M 77.3 / 73.1, 30M 934 / 879, 200M 10037 / 5722.
+constexpr int64_t kManyWeights = 4 << 20, kManyCounts = 2 << 20;
 
 __device__ __forceinline__ double dens_weight(float o_or_sigma, int mode)
 {
@@ -96,9 +102,22 @@ __global__ __launch_bounds__(kDensBlock) void k_weight_partial(const float* __re
     if (threadIdx.x == 0) partial[blockIdx.x] = tot;
 }
 
+// The sum of the partial sums, in the order in which k_select would add them.
+__global__ __launch_bounds__(kDensBlock) void k_weight_total(const double* __restrict__ partial,
+                                                             int64_t np, double* __restrict__ total)
+{
+    __shared__ double s[kDensBlock];
+    double acc = 0.0;
+#pragma unroll 8
+    for (int64_t j = threadIdx.x; j < np; j += kDensBlock) acc += partial[j];
+    const double tot = block_sum(acc, s);
+    if (threadIdx.x == 0) total[0] = tot;
+}
+
 // p_i = min(1, k w_i / sum w); selected iff u_i < p_i (all in FP64).  Every
-// workgroup adds the partial sums itself, in the same fixed order (a launch
-// less; 733 sums at 3M triangles).
+// workgroup adds the np partial sums itself, in the same fixed order (a launch
+// less; 733 sums at 3M triangles); of a larger soup, whose workgroups and sums
+// both grow, it gets their total as the only one.
 __global__ __launch_bounds__(kDensBlock) void k_select(const float* __restrict__ x, int64_t N,
                                                        int mode, double k,
                                                        const double* __restrict__ partial,
@@ -169,6 +188,18 @@ __global__ __launch_bounds__(kDensBlock) void k_count_sel(const uint8_t* __restr
     if (threadIdx.x == 0) cnt[blockIdx.x] = c;
 }
 
+// Sums of kSpan counts each.
+constexpr int kSpan = kDensBlock;
+
+__global__ __launch_bounds__(kDensBlock) void k_sum_counts(const uint32_t* __restrict__ cnt,
+                                                           int64_t nb, uint32_t* __restrict__ span)
+{
+    __shared__ uint32_t s_w[kDensBlock / kWave];
+    const int64_t j = (int64_t)blockIdx.x * kSpan + threadIdx.x;
+    const uint32_t c = block_sum_u32(j < nb ? cnt[j] : 0u, s_w);
+    if (threadIdx.x == 0) span[blockIdx.x] = c;
+}
+
 // Midpoint subdivision in place: the centre child replaces the parent, the
 // three corner children go to N + 3 r + {0, 1, 2}, r the rank of the
 // parent among the selected triangles; they copy its opacity, sigma and SH
@@ -176,7 +207,7 @@ __global__ __launch_bounds__(kDensBlock) void k_count_sel(const uint8_t* __restr
 //
 // A workgroup takes a chunk of triangles: it adds the counts of the chunks
 // before it (and of all, for the capacity test: nothing is written when the
-// soup does not fit), lists its selected triangles in LDS, and writes the
+// soup does not fit; SPANS: by their sums over spans of chunks), lists its selected triangles in LDS, and writes the
 // children of consecutive ranks, which are contiguous, element by element.
 // Bound by HBM (the SH rows: 192 bytes read and 576 written per selected
 // triangle): with a wave copying one selected row at a time, each row's load
@@ -186,11 +217,12 @@ __global__ __launch_bounds__(kDensBlock) void k_count_sel(const uint8_t* __restr
 // lines; 123 us in one workgroup with ordinary stores).
 constexpr int kBatchSel = 256;   // selected triangles whose vertices are staged at once
 
-template <int F>
+template <int F, bool SPANS>
 __global__ __launch_bounds__(kDensBlock) void k_subdivide(
     float* __restrict__ v, float* __restrict__ o, float* __restrict__ sigma, float* __restrict__ sh,
     int nsh, int64_t N, int64_t capacity, const uint8_t* __restrict__ sel,
-    const uint32_t* __restrict__ cnt, int64_t nb, uint32_t* __restrict__ out)
+    const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ span, int64_t nb,
+    uint32_t* __restrict__ out)
 {
     __shared__ uint16_t s_id[F * kDensBlock];   // selected triangles of the chunk, in order
     __shared__ float s_p[kBatchSel][9];
@@ -202,10 +234,21 @@ __global__ __launch_bounds__(kDensBlock) void k_subdivide(
     if (tid < 2) s_sum[tid] = 0ull;
     __syncthreads();
     unsigned long long before = 0, all = 0;
-    for (int64_t j = tid; j < nb; j += kDensBlock) {
-        const uint32_t c = cnt[j];
-        all += c;
-        before += j < (int64_t)blockIdx.x ? c : 0u;
+    const int64_t mine = blockIdx.x;
+    if constexpr (SPANS) {
+        const int64_t own = mine / kSpan, j = own * kSpan + tid;
+        for (int64_t k = tid; k < (nb + kSpan - 1) / kSpan; k += kDensBlock) {
+            const uint32_t c = span[k];
+            all += c;
+            before += k < own ? c : 0u;
+        }
+        before += j < mine ? cnt[j] : 0u;
+    } else {
+        for (int64_t j = tid; j < nb; j += kDensBlock) {
+            const uint32_t c = cnt[j];
+            all += c;
+            before += j < mine ? c : 0u;
+        }
     }
     // integer sums: the order does not matter
     atomicAdd(&s_sum[0], before);
@@ -323,8 +366,13 @@ void launch_densify_select(const float* o, const float* sigma, int64_t N, int mo
     const float* x = mode == TS_DENSIFY_OPACITY ? o : sigma;
     hipLaunchKernelGGL(k_weight_partial, dim3((unsigned)nw), dim3(kDensBlock), 0, stream, x, N,
                        mode, partial);
+    const bool total = N > kManyWeights;
+    if (total)
+        hipLaunchKernelGGL(k_weight_total, dim3(1), dim3(kDensBlock), 0, stream,
+                           (const double*)partial, nw, partial + nw);
     hipLaunchKernelGGL(k_select, dim3((unsigned)((N + kPickChunk - 1) / kPickChunk)),
-                       dim3(kDensBlock), 0, stream, x, N, mode, k, (const double*)partial, nw, u,
+                       dim3(kDensBlock), 0, stream, x, N, mode, k,
+                       (const double*)(total ? partial + nw : partial), total ? (int64_t)1 : nw, u,
                        sel);
 }
 
@@ -333,16 +381,25 @@ void launch_densify_subdivide(float* v, float* o, float* sigma, float* sh, int n
                               hipStream_t stream)
 {
     uint32_t* cnt = reinterpret_cast<uint32_t*>(ws);
-    auto go = [&](auto per_thread) {
+    auto go = [&](auto per_thread, auto spans) {
         constexpr int F = decltype(per_thread)::value;
+        constexpr bool SPANS = decltype(spans)::value;
         const int64_t nb = (N + F * kDensBlock - 1) / (F * kDensBlock);
+        uint32_t* span = cnt + nb;
         hipLaunchKernelGGL(k_count_sel<F>, dim3((unsigned)nb), dim3(kDensBlock), 0, stream, sel, N,
                            cnt);
-        hipLaunchKernelGGL(k_subdivide<F>, dim3((unsigned)nb, 2), dim3(kDensBlock), 0, stream, v,
-                           o, sigma, sh, nsh, N, capacity, sel, (const uint32_t*)cnt, nb, d_out);
+        if (SPANS)
+            hipLaunchKernelGGL(k_sum_counts, dim3((unsigned)((nb + kSpan - 1) / kSpan)),
+                               dim3(kDensBlock), 0, stream, (const uint32_t*)cnt, nb, span);
+        hipLaunchKernelGGL((k_subdivide<F, SPANS>), dim3((unsigned)nb, 2), dim3(kDensBlock), 0,
+                           stream, v, o, sigma, sh, nsh, N, capacity, sel, (const uint32_t*)cnt,
+                           (const uint32_t*)span, nb, d_out);
     };
-    if (N > kFewTriangles) go(std::integral_constant<int, kMany>{});
-    else go(std::integral_constant<int, kFew>{});
+    const std::integral_constant<int, kFew> few;
+    const std::integral_constant<int, kMany> many;
+    if (N <= kFewTriangles) go(few, std::false_type{});
+    else if (N <= kManyCounts) go(many, std::false_type{});
+    else go(many, std::true_type{});
 }
 
 }  // namespace ts

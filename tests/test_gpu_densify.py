@@ -171,3 +171,57 @@ def test_select_from_unaligned_arrays():
     assert got[0] == 0
     assert np.array_equal(got[1:].astype(bool), _select(o[1:], o[1:], B.TS_DENSIFY_OPACITY, 700.0,
                                                         u[1:]))
+
+
+# Around the sizes from which the sums get launches of their own: the same
+# decisions and children on both sides.
+@pytest.mark.parametrize("N", [1 << 22, (1 << 22) + 1, 9_000_001])
+def test_select_of_large_soups(N):
+    rng = np.random.default_rng(34)
+    o, u = (rng.random(N).astype(np.float32) for _ in range(2))
+    assert _check_select(o, o, B.TS_DENSIFY_OPACITY, 0.1 * N, u) > 0
+
+
+@pytest.mark.parametrize("N,share", [(1 << 21, 0.1), ((1 << 21) + 1, 0.1), ((1 << 21) + 1, 1.0),
+                                     (1025 * 2048 + 7, 0.0), (5_000_003, 0.3)])
+def test_subdivide_of_large_soups(N, share):
+    v, o, s, sh = _soup(35, N, 0)
+    sel = np.random.default_rng(36).random(N) < share
+    n = int(sel.sum())
+    gv, go, gs, gsh, d = _subdivide(v, o, s, sh, 0, sel, N + 3 * n)
+    wv, wo, ws_, wsh = D.subdivide(v, o, s, sh, sel)
+    assert d[0] == N + 3 * n and d[1] == 0
+    for got, want in ((gv, wv), (go, wo), (gs, ws_), (gsh, wsh)):
+        assert np.array_equal(got, want)
+    if n:   # one slot too few
+        with pytest.raises(B.TSError) as e:
+            _subdivide(v, o, s, sh, 0, sel, N + 3 * n - 1)
+        assert e.value.code == B.TS_ECAPACITY
+
+
+def test_densify_time_grows_with_the_soup():
+    """Ten times the triangles take less than twenty times as long: no work that
+    grows with the square of the soup."""
+    def passes(n):
+        cap = n + n // 8
+        o, s, u = torch.rand(cap, device=DEV), torch.rand(cap, device=DEV), torch.rand(n, device=DEV)
+        v, sh = torch.zeros(cap, 3, 3, device=DEV), torch.zeros(cap, 1, 3, device=DEV)
+        sel = torch.empty(n, dtype=torch.uint8, device=DEV)
+        nb = B.ts_densify_workspace_bytes(n)
+        ws = torch.empty(nb, dtype=torch.uint8, device=DEV)
+        d = torch.zeros(2, dtype=torch.int32, device=DEV)
+        best = [1e9, 1e9]
+        for _ in range(6):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(3)]
+            e[0].record()
+            B.ts_densify_select(o, s, n, B.TS_DENSIFY_OPACITY, 0.03 * n, u, sel, ws, nb)
+            e[1].record()
+            B.ts_densify_subdivide(v, o, s, sh, 0, n, cap, sel, ws, nb, d)
+            e[2].record()
+            torch.cuda.synchronize()
+            best = [min(best[k], e[k].elapsed_time(e[k + 1])) for k in range(2)]
+        assert d.tolist()[1] == 0
+        return best
+
+    small, large = passes(10_000_000), passes(100_000_000)
+    assert all(b < 20 * a for a, b in zip(small, large)), (small, large)
