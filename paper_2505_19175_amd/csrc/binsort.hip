@@ -803,6 +803,29 @@ __device__ __forceinline__ uint32_t for_group_tiles(int G, int g,
     return vis;
 }
 
+// The batch's tiles [lo, hi) that group g of G meets, of the Ta there are: those
+// of its view, or all where groups take several views.  A group leaves the other
+// windows alone: with every window walked by every group, a batch of eight 4K
+// views of 1.9M triangles (16 windows) took 4.75 ms instead of 3.17, eight 8K
+// views 25.1 instead of 12.1 (the radix chain 4.22 and 15.0).
+__device__ __forceinline__ void group_tiles(int G, int g, const TileGrid& tg, int Ta, int& lo,
+                                            int& hi)
+{
+    const int64_t N = tg.d_n ? (int64_t)*tg.d_n : tg.N;
+    const int nv = (int)((N + tg.per_view - 1) / tg.per_view);
+    lo = 0;
+    hi = Ta;
+    if (nv > G) return;
+    const int v = nv > 0 ? g / max(1, G / nv) : 0;
+    if (v >= nv) {
+        hi = 0;   // no entries
+        return;
+    }
+    const ts_view& V = tg.views[v];
+    lo = (int)min(V.tile_offset, (uint32_t)Ta);
+    hi = min(Ta, lo + (int)V.tiles_x * ((V.cam.height + kTile - 1) / kTile));
+}
+
 // Sum of one value per thread over the workgroup, in thread 0.
 __device__ __forceinline__ uint32_t group_sum(uint32_t v, uint32_t* s_tmp)
 {
@@ -988,8 +1011,18 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_count(
              f += (int64_t)gridDim.x * kGroupThreads)
             ranges[f] = 0u;
     uint32_t* row = hist + (int64_t)g * T;
+    int lo = 0, hi = Ta;
+    if constexpr (WIDE) {
+        group_tiles(G, g, tg, Ta, lo, hi);
+        if (tid == 0) grp[g] = 0u;
+    }
     for (int w0 = 0;; w0 += kWideTiles) {   // windows of tiles; one unless WIDE
         const int m = WIDE ? min(kWideTiles, Ta - w0) : Ta;
+        if (WIDE && (hi <= w0 || lo >= w0 + m)) {   // none of the group's tiles
+            for (int t = tid; t < m; t += kGroupThreads) row[w0 + t] = 0u;
+            if (w0 + kWideTiles >= Ta) return;
+            continue;
+        }
         const int words = WIDE ? (m + 1) / 2 : m;
         for (int t = tid; t < words; t += kGroupThreads) s_h[t] = 0u;
         __syncthreads();
@@ -1179,8 +1212,11 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place_wide(
     const int g = xcd_group((int)blockIdx.x - 1, G);
     const uint32_t* row = hist + (int64_t)g * T;
     const bool full = *o.d_ovf != 0u;
+    int lo, hi;
+    group_tiles(G, g, tg, Ta, lo, hi);
     for (int w0 = 0; w0 < Ta; w0 += kWideTiles) {
         const int m = min(kWideTiles, Ta - w0);
+        if (hi <= w0 || lo >= w0 + m) continue;   // none of the group's tiles
         __syncthreads();
         for (int t = tid; t < m; t += kGroupThreads)
             s_t[t] = first_slot(start[w0 + t], row[w0 + t], o.capacity);

@@ -240,3 +240,64 @@ def test_short_lists_on_another_stream():
         assert st.M == ref.M and st.capacity >= ref.M and len(junk) == 4
         for a, b in ((out.rgb, want.rgb), (out.alpha, want.alpha), (out.depth, want.depth)):
             assert torch.equal(a, b)
+
+
+# Views in windows of their own, across a window's edge and beyond it, small views
+# that share one, and (the second set) more views than groups.
+@pytest.mark.parametrize("n,sizes", [
+    (30_000, [(2100, 2048), (64, 48), (1920, 1080), (333, 200), (2048, 2063), (16, 16)]),
+    (40, [(2100, 2048), (64, 48), (1920, 1080), (333, 200), (2048, 2063), (16, 16)])])
+def test_batch_of_many_windows(n, sizes):
+    rng = np.random.Generator(np.random.PCG64(6))
+    sc = synth.cluster_soup(6, n, extent=3.0, std=0.4, edge_median=0.05, sh_degree=0, rng=rng)
+    cfg = synth.Config(sh_degree=0)
+    scene = scene_to_device(sc, DEV)
+    cams = [synth.look_at(e, width=w, height=h)
+            for e, (w, h) in zip(synth.hemisphere_eyes(rng, len(sizes)), sizes)]
+    ex = BatchedExecutor(scene, cfg, time.perf_counter, max_views=len(sizes), max_tiles=70_000,
+                         max_pixels=sum(w * h for w, h in sizes), capacity=1 << 22, slots=1)
+    for pick in ([0, 1, 2, 3, 4, 5], [4, 5], [5, 3, 0, 2], [1], [2, 0]):
+        batch = [Request(i, cams[i], 0.0) for i in pick]
+        ex.submit(0, batch)
+        while (res := ex.poll(0)) is None:
+            pass
+        assert not res.overflow
+        total = 0
+        for i, got in zip(pick, ex.outputs(0, batch)):
+            st = ViewState(n, cams[i].width, cams[i].height, 1 << 21)
+            out = Rasterizer(cfg).forward(st, scene, cams[i], sync=True)
+            total += st.M
+            for a, b in zip(got, (out.rgb, out.alpha, out.depth)):
+                assert torch.equal(a, b)
+        assert res.instances == total
+
+
+def test_batch_time_does_not_grow_with_its_windows():
+    """What a soup adds to a batch's time (no triangle is visible, so walking it is
+    all there is): over 16 windows of tiles no more than twice what it adds over
+    one."""
+    def ms(n, w, h):
+        v = torch.zeros(n, 3, 3, device=DEV)
+        v[:, :, 2] = -5.0
+        one = torch.ones(n, device=DEV)
+        ex = BatchedExecutor((v, one, one, torch.zeros(n, 1, 3, device=DEV)),
+                             synth.Config(sh_degree=0), time.perf_counter, max_views=8,
+                             max_tiles=8 * 32400, max_pixels=8 * w * h, capacity=1 << 16, slots=1)
+        cam = synth.identity_camera(w, h)
+        ex.submit(0, [Request(i, cam, 0.0) for i in range(8)])
+        torch.cuda.synchronize()
+        s, best = ex._slots[0], 1e9
+        with torch.cuda.stream(s.stream):
+            for _ in range(8):
+                e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                e[0].record()
+                s.graph.replay()
+                e[1].record()
+                torch.cuda.synchronize()
+                best = min(best, e[0].elapsed_time(e[1]))
+        return best
+
+    big, few = 2_000_000, 40_000   # 256 groups either way: the same matrix of counts
+    many = ms(big, 3840, 2160) - ms(few, 3840, 2160)
+    one = ms(big, 640, 360) - ms(few, 640, 360)
+    assert 0.0 < many < 2.0 * one, (many, one)
