@@ -97,47 +97,56 @@ struct FwdStage : StageExtra<WIN, kBatch> {
     __device__ uint32_t* tri() { return words + kWaveList; }
 };
 
-constexpr int kWideImage = 1024;         // fewest tiles of an image that has wide entries summed
-constexpr int kWideSlots = 10;            // what 25 LDS allocation units leave room for
-constexpr int kWideBlocks = 8;            // blocks of the tile that make an entry wide (4, 6: +1 us at 3M)
+// fewest tiles of an image that has wide entries summed
+constexpr int kWideImage = 1024, kWideImageSigmoid = 800;
+constexpr int kWideSlots = 10;           // what 25 LDS allocation units leave room for
+constexpr int kWideBlocks = 8;           // blocks of the tile that make an entry wide (4, 6: +1 us at 3M)
 constexpr uint32_t kWideTri = 0xffffff00u;   // above any triangle: a slot, not a triangle
 
-// The backward's LDS.  Sigmoid window: its triangles cover most blocks of many
-// tiles, so the entries' 2D gradients are summed over the tile's blocks here
-// (batches of 128 entries: the sums take 64 bytes each) and an entry costs one
-// row of global atomics per tile instead of one per 4x4 block: raster backward
-// of 300k triangles (1788 entries per tile) 0.660 -> 0.503 ms.  The other
-// windows' triangles meet 1-2 blocks of a tile, and the LDS sums cost more than
-// the rows saved (3M triangles 0.156 -> 0.193 ms, 20k 0.040 -> 0.055 ms).  Pixel
-// quads as the backward's cells, as in the forward: fewer vector instructions
-// (77.0M -> 70.1M at 3M) but 1.5 times the lines of atomics, and slower (0.153
-// -> 0.195 ms, 300k 0.0245 -> 0.0477 ms).
+// The backward's LDS.  The gradients of an entry take one line of global atomics
+// for each 4x4 block of the tile that composited it: 1-2 blocks for most
+// triangles of a scene, which LDS sums would not pay for (3M triangles 0.156 ->
+// 0.193 ms, 20k 0.040 -> 0.055 ms).  Pixel quads as the backward's cells, as in
+// the forward: fewer vector instructions (77.0M -> 70.1M at 3M) but 1.5 times
+// the lines of atomics, and slower (0.153 -> 0.195 ms, 300k 0.0245 -> 0.0477 ms).
 //
 // Wide entries (W): where a few triangles cover many tiles, their lines take an
 // atomic per block from all over the chip, one after another.  In a batch the
-// first kWideSlots entries that composited in half a tile's blocks are summed
-// here and cost one row per tile; their zt holds the slot instead of the
-// triangle.  Raster backward of a 300k-triangle cluster view with such
-// triangles 63.9 -> 22 us; the LogSumExp step of four 300k soups 119-136 ->
-// 107-115 us.  A step pays one comparison more (3M triangles 137.1 -> 139.1 us,
-// 20k at 256x256 34.6 -> 35.5), so small images, where no triangle covers many
-// tiles, go without.
+// first kSlots entries that composited in half a tile's blocks are summed here
+// and cost one row per tile; their zt holds the slot instead of the triangle.
+// Raster backward of a 300k-triangle cluster view with such triangles 63.9 -> 22
+// us; the LogSumExp step of four 300k soups 119-136 -> 107-115 us.  A step pays
+// one comparison more (3M triangles 137.1 -> 139.1 us, 20k at 256x256 34.6 ->
+// 35.5, a LogSumExp soup with few wide triangles 29.7 -> 31.2).  Images of fewer
+// than kWideImage tiles go without: soups of small triangles would lose 2-4%
+// there (300k at 640x360 16.0 -> 16.4 us), those with wide ones gain (2k triangles
+// of edge 1 at 256x256 64.6 -> 36.7, at 640x360 265 -> 85).
+//
+// Sigmoid window: its triangles cover most blocks of many tiles, so there is a
+// slot for every entry of a batch (of 128: the slots take 64 bytes each).  Raster
+// backward of 300k triangles (1788 entries per tile) 580 -> 381 us, and 423 with
+// every entry summed here; 1M of a fifth of the sigma (3.3 blocks an entry) 265
+// -> 251, and 287 with every entry.  In small images the halved batches cost more
+// than the lines saved: without slots / with, dense and narrow soups, 256 tiles
+// 119 / 141 and 10.5 / 11.5 us, 768 tiles 184 / 192 and 20.7 / 22.0, 920 tiles 86
+// / 70 and 20.9 / 22.2, 1850 tiles 151 / 105 and 18.8 / 17.4.  The stored-fragment
+// form (WIDE and SF) sums every entry, in images of any size: 300k triangles 1.89
+// ms, 1.99 with the wide ones only, 2.51 with none.
 template <int WIN, bool W>
-struct BwdStage : StageBase<WIN, kBatch> {
-    static constexpr bool kSums = false;
-};
+struct BwdStage : StageBase<WIN, kBatch> {};
 template <int WIN>
 struct BwdStage<WIN, true> : StageBase<WIN, kBatch> {
-    static constexpr bool kSums = false;
+    static constexpr int kSlots = kWideSlots;
     uint32_t wide[2];              // wide entries of this batch and of the one before
-    uint32_t tri[2][kWideSlots];   // their triangles
-    float acc[kWideSlots * TS_G2D_STRIDE];
+    uint32_t tri[2][kSlots];       // their triangles
+    float acc[kSlots * TS_G2D_STRIDE];
 };
 template <>
-struct BwdStage<TS_WINDOW_SIGMOID, false> : StageBase<TS_WINDOW_SIGMOID, 128> {
-    static constexpr bool kSums = true;
-    uint32_t tri[2][128];   // of this batch and of the one whose sums are written
-    float acc[128 * TS_G2D_STRIDE];
+struct BwdStage<TS_WINDOW_SIGMOID, true> : StageBase<TS_WINDOW_SIGMOID, 128> {
+    static constexpr int kSlots = 128;
+    uint32_t wide[2];
+    uint32_t tri[2][kSlots];
+    float acc[kSlots * TS_G2D_STRIDE];
 };
 
 union RecView {
@@ -903,11 +912,11 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
     __syncthreads();
     const uint32_t jmax = s_max;   // entries any pixel of the tile needs
 
-    constexpr bool SUMS = BwdStage<WIN, WIDE>::kSums;
     constexpr int NB = BwdStage<WIN, WIDE>::kN;
+    constexpr bool ALL = WIDE && SF;   // every entry is summed, in the slot of its thread
     // a batch's sums -> the triangles' accumulators, and zeros again
     auto flush = [&](int n, int b) {
-        if constexpr (SUMS || WIDE) {
+        if constexpr (WIDE) {
             for (int f = tid; f < n * TS_G2D_STRIDE; f += kBlock) {
                 const float x = S.acc[f];
                 if (x != 0.f) {
@@ -918,13 +927,11 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
             }
         }
     };
-    if constexpr (SUMS || WIDE)
-        for (int f = tid; f < (SUMS ? NB : kWideSlots) * TS_G2D_STRIDE; f += kBlock)
-            S.acc[f] = 0.f;
     if constexpr (WIDE) {
+        for (int f = tid; f < S.kSlots * TS_G2D_STRIDE; f += kBlock) S.acc[f] = 0.f;
         if (tid < 2) S.wide[tid] = 0u;
     }
-    int last_n = 0, par = 0;
+    int par = 0;
     // entry to stage, loaded a batch ahead
     const uint32_t lo0 = jmax > (uint32_t)NB ? jmax - NB : 0u;
     uint32_t next = tid < (int)(jmax - lo0) ? vals[start + lo0 + tid] : 0u;
@@ -932,17 +939,10 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
         const uint32_t lo_ = hi_ > (uint32_t)NB ? hi_ - NB : 0u;
         const int n = (int)(hi_ - lo_);
         __syncthreads();
-        if constexpr (SUMS) {
-            flush(last_n, par);
-            last_n = n;
-        }
-        if constexpr (WIDE) {
-            flush((int)min(S.wide[par], (uint32_t)kWideSlots), par);
-        }
+        if constexpr (WIDE) flush((int)min(S.wide[par], (uint32_t)S.kSlots), par);
         par ^= 1;
         if (tid < n) {
             const uint32_t tri = next;
-            if constexpr (SUMS) S.tri[par][tid] = tri;
             if (blocks) {   // the forward's record of where the entry composited
                 stage_copy(S, rec, tri, tx * kTile, ty * kTile);
                 S.hit[tid] = blocks[start + lo_ + tid];
@@ -950,9 +950,12 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
                 S.hit[tid] = (uint16_t)stage_rec(S, rec, tri, tx * kTile, ty * kTile);
             }
             if constexpr (WIDE) {
-                if (__popc(S.hit[tid]) >= kWideBlocks) {
+                if constexpr (ALL) {
+                    S.tri[par][tid] = tri;
+                    if (tid == 0) S.wide[par] = (uint32_t)n;
+                } else if (__popc(S.hit[tid]) >= kWideBlocks) {
                     const uint32_t slot = atomicAdd(&S.wide[par], 1u);
-                    if (slot < (uint32_t)kWideSlots) {
+                    if (slot < (uint32_t)S.kSlots) {
                         S.tri[par][slot] = tri;
                         S.zt[tid].y = kWideTri + slot;
                     }
@@ -1083,24 +1086,21 @@ __global__ __launch_bounds__(256) void k_raster_bwd(
             constexpr uint64_t slots =
                 WIN == TS_WINDOW_LSE ? ~0ull : 0x7fff7fff7fff7fffull;
             if (lanes(act & slots & ballot64(tot != 0.f))) {
-                if constexpr (SUMS) {
-                    unsafeAtomicAdd(&S.acc[jc * TS_G2D_STRIDE + P.i], tot);
-                } else {
-                    if (WIDE && tri >= kWideTri) {
-                        if constexpr (WIDE)
-                            unsafeAtomicAdd(&S.acc[(tri - kWideTri) * TS_G2D_STRIDE + P.i], tot);
-                    } else {
-                        unsafeAtomicAdd(g2d + (int64_t)tri * TS_G2D_STRIDE + P.i, tot);
+                if (ALL || (WIDE && tri >= kWideTri)) {
+                    if constexpr (WIDE) {
+                        const uint32_t slot = ALL ? (uint32_t)jc : tri - kWideTri;
+                        unsafeAtomicAdd(&S.acc[slot * TS_G2D_STRIDE + P.i], tot);
                     }
+                } else {
+                    unsafeAtomicAdd(g2d + (int64_t)tri * TS_G2D_STRIDE + P.i, tot);
                 }
             }
         }
         hi_ = lo_;
     }
-    if constexpr (SUMS || WIDE) {
+    if constexpr (WIDE) {
         __syncthreads();
-        if constexpr (SUMS) flush(last_n, par);
-        else flush((int)min(S.wide[par], (uint32_t)kWideSlots), par);
+        flush((int)min(S.wide[par], (uint32_t)S.kSlots), par);
     }
 }
 
@@ -1180,21 +1180,23 @@ void launch_raster_backward(const void* rec, const uint32_t* vals, const uint32_
     };
     if (fs) {
         switch (cfg.window) {
-        case TS_WINDOW_SIGMOID: go(k_raster_bwd<TS_WINDOW_SIGMOID, true>); break;
+        case TS_WINDOW_SIGMOID: go(k_raster_bwd<TS_WINDOW_SIGMOID, true, true>); break;
         case TS_WINDOW_LSE: go(k_raster_bwd<TS_WINDOW_LSE, true>); break;
         default: go(k_raster_bwd<TS_WINDOW_PAPER, true>); break;
         }
         return;
     }
+    const bool wide =
+        num_tiles >= (cfg.window == TS_WINDOW_SIGMOID ? kWideImageSigmoid : kWideImage);
     switch (cfg.window) {
-    case TS_WINDOW_SIGMOID: go(k_raster_bwd<TS_WINDOW_SIGMOID>); break;
+    case TS_WINDOW_SIGMOID:
+        wide ? go(k_raster_bwd<TS_WINDOW_SIGMOID, false, true>) : go(k_raster_bwd<TS_WINDOW_SIGMOID>);
+        break;
     case TS_WINDOW_LSE:
-        if (num_tiles >= kWideImage) go(k_raster_bwd<TS_WINDOW_LSE, false, true>);
-        else go(k_raster_bwd<TS_WINDOW_LSE>);
+        wide ? go(k_raster_bwd<TS_WINDOW_LSE, false, true>) : go(k_raster_bwd<TS_WINDOW_LSE>);
         break;
     default:
-        if (num_tiles >= kWideImage) go(k_raster_bwd<TS_WINDOW_PAPER, false, true>);
-        else go(k_raster_bwd<TS_WINDOW_PAPER>);
+        wide ? go(k_raster_bwd<TS_WINDOW_PAPER, false, true>) : go(k_raster_bwd<TS_WINDOW_PAPER>);
         break;
     }
 }

@@ -57,6 +57,30 @@ def test_wide_entries(n, window):
     G.assert_grads(g, O.backward(sc, cam, cfg, dC, dA, dD))
 
 
+# The sigmoid window sums the wide entries of an image of 800 tiles or more,
+# batches of 128 entries: narrow ones between them (sigma well below the pixel),
+# and all of a batch wide.
+@pytest.mark.parametrize("W,H", [(512, 400), (496, 400)])   # 800 tiles, and 775: without the sums
+@pytest.mark.parametrize("n,narrow", [(1, 200), (127, 0), (128, 1), (300, 200)])
+def test_wide_entries_of_the_sigmoid(n, narrow, W, H):
+    wide, cam = random_soup(71, n, W=W, H=H, size=1.5, deg=1, sigma=(0.3, 2.0), o=(0.02, 0.1),
+                            dtype=np.float32)
+    small, _ = random_soup(72, max(narrow, 1), W=W, H=H, size=0.05, deg=1, sigma=(0.01, 0.05),
+                           o=(0.2, 0.9), dtype=np.float32)
+    sc = wide if narrow == 0 else type(wide)(*(np.concatenate([a, b]) for a, b in
+                                               zip((small.v, small.o, small.sigma, small.sh),
+                                                   (wide.v, wide.o, wide.sigma, wide.sh))))
+    cfg = Config(sh_degree=1, bg=(0.1, 0.2, 0.3), window=WINDOW_SIGMOID)
+    ras, st, sct, out = G.gpu_forward(sc, cam, cfg, capacity=1 << 20)
+    ref = O.render(sc, cam, cfg)
+    G.assert_forward(G.to_np(out), ref, resolve=(sc, cam, cfg, True))
+    dC, dA, dD = synth.upstream(n, cam.width, cam.height, True, True)
+    keep = ref["flag"] == 0
+    dC, dA, dD = dC * keep[None], dA * keep, dD * keep
+    g = G.gpu_backward(ras, st, sct, out, dC, dA, dD)
+    G.assert_grads(g, O.backward(sc, cam, cfg, dC, dA, dD))
+
+
 @pytest.mark.parametrize("window,sigma", [(WINDOW_PAPER, 1.0), (WINDOW_SIGMOID, 0.05),
                                           (WINDOW_LSE, 1.0)])
 @pytest.mark.parametrize("W,H", [(16, 16), (528, 512)])   # the second sums wide entries
