@@ -301,3 +301,96 @@ def test_batch_time_does_not_grow_with_its_windows():
     many = ms(big, 3840, 2160) - ms(few, 3840, 2160)
     one = ms(big, 640, 360) - ms(few, 640, 360)
     assert 0.0 < many < 2.0 * one, (many, one)
+
+
+def _batch_against_single_views(scene, cfg, cams, n, **kw):
+    """A batch's frames and instance count against the views rendered alone; returns
+    the executor."""
+    ex = BatchedExecutor(scene, cfg, time.perf_counter, slots=1, **kw)
+    alone = {}
+    for pick in (range(len(cams)), range(len(cams) // 2, len(cams))):   # replays
+        batch = [Request(i, cams[i], 0.0) for i in pick]
+        ex.submit(0, batch)
+        while (res := ex.poll(0)) is None:
+            pass
+        assert not res.overflow
+        total = 0
+        for i, got in zip(pick, ex.outputs(0, batch)):
+            key = id(cams[i])
+            if key not in alone:
+                st = ViewState(n, cams[i].width, cams[i].height, 1 << 20)
+                out = Rasterizer(cfg).forward(st, scene, cams[i], sync=True)
+                alone[key] = st.M, out
+            total += alone[key][0]
+            out = alone[key][1]
+            for a, b in zip(got, (out.rgb, out.alpha, out.depth)):
+                assert torch.equal(a, b)
+        assert res.instances == total
+    return ex
+
+
+# 128 views of one tile that every triangle covers, so a group's 16-bit counter
+# holds all of its entries: 65528 at most (the last size that is counted by
+# groups), and one triangle more, which takes the radix chain.
+@pytest.mark.parametrize("n", [131_042, 131_043])
+def test_batch_at_the_most_entries_of_a_group(n):
+    scene = scene_to_device(_covering(n), DEV)
+    cams = [synth.identity_camera(16, 16), synth.identity_camera(16, 15)] * 64
+    _batch_against_single_views(scene, synth.Config(sh_degree=0), cams, n, max_views=128,
+                                max_tiles=20_000, max_pixels=128 * 256, capacity=17_000_000)
+
+
+# The radix chain of a batch: more views than groups (257), and a soup too large for
+# the groups' counters with the default eight views.
+@pytest.mark.parametrize("n,views,sizes", [
+    (300, 257, [(640, 360), (333, 200), (64, 48), (1920, 1080), (16, 16)]),
+    (2_200_000, 8, [(640, 360), (1280, 720), (333, 200)])])
+def test_batch_by_the_radix_chain(n, views, sizes):
+    rng = np.random.Generator(np.random.PCG64(9))
+    sc = synth.cluster_soup(9, n, extent=3.0, std=0.4, edge_median=0.05 if n < 1000 else 0.005,
+                            sh_degree=0, rng=rng)
+    scene = scene_to_device(sc, DEV)
+    cams = [synth.look_at(e, width=w, height=h)
+            for e, (w, h) in zip(synth.hemisphere_eyes(rng, len(sizes)), sizes)]
+    kw = dict(max_views=views, max_tiles=20_000, max_pixels=sum(w * h for w, h in sizes))
+    cfg = synth.Config(sh_degree=0)
+    ex = _batch_against_single_views(scene, cfg, cams, n, capacity=1 << 23, **kw)
+    # lists for half of the first batch's instances: flagged, runs inside the lists
+    batch = [Request(i, c, 0.0) for i, c in enumerate(cams)]
+    ex.submit(0, batch)
+    while (res := ex.poll(0)) is None:
+        pass
+    cap = res.instances // 2
+    ex = BatchedExecutor(scene, cfg, time.perf_counter, slots=1, capacity=cap, **kw)
+    ex.submit(0, batch)
+    while (short := ex.poll(0)) is None:
+        pass
+    assert short.overflow and short.instances == res.instances
+    r = ex._slots[0].ranges.cpu().numpy()
+    assert r.min() >= 0 and r.max() == cap and (r[:, 1] - r[:, 0]).sum() == cap
+
+
+@pytest.mark.parametrize("mul", [1, 40])
+def test_view_of_more_tiles_than_the_groups_count(mul):
+    """A 3840x2160 view (32400 tiles: the radix chain), its counts read after the
+    render and its launches sized by the lists: the same as with the counts read
+    first, for lists that fit, are far too long, and are too short."""
+    n, W, H = 30_000, 3840, 2160
+    rng = np.random.Generator(np.random.PCG64(10))
+    sc = synth.cluster_soup(10, n, extent=2.0, std=0.4, edge_median=0.05, sh_degree=0, rng=rng)
+    scene, cfg = scene_to_device(sc, DEV), synth.Config(sh_degree=0)
+    cam = synth.look_at(synth.hemisphere_eyes(rng, 1)[0], width=W, height=H)
+    ras, ref = Rasterizer(cfg), ViewState(n, W, H, 1 << 20)
+    cc = ras.project(ref, scene, cam)
+    ras.bin_sort(ref, cc)                       # the counts first
+    ref.ccam = cc
+    want = ref.outputs()
+    B.ts_render_forward(ref.proj, ref.bins, cc, ras.ccfg, want.rgb, want.alpha, want.depth,
+                        want.T_final, want.last, torch.cuda.current_stream().cuda_stream)
+    for cap in (ref.M * mul, ref.M // 3):
+        st = ViewState(n, W, H, cap)
+        out = ras.forward(st, scene, cam, sync=True)
+        assert (st.M, st.N_v) == (ref.M, ref.N_v) and st.capacity >= ref.M
+        assert torch.equal(st.vals[:st.M], ref.vals[:st.M]) and torch.equal(st.ranges, ref.ranges)
+        for a, b in ((out.rgb, want.rgb), (out.alpha, want.alpha), (out.depth, want.depth)):
+            assert torch.equal(a, b)
