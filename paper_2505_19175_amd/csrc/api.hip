@@ -510,8 +510,8 @@ int ts_render_forward_batched(const float* v, const float* o, const float* sigma
     if (!ws || ws_bytes < need.bytes + 256)
         return fail(TS_EWORKSPACE, "ts_render_forward_batched: workspace too small");
     const ts::BinWorkspace w = ts::carve_bin_workspace(ws, entries, bins->capacity, (int64_t)max_tiles);
-    uint32_t* extra = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(ws) + need.bytes);
-    uint32_t* bctl = extra + 4;     // clamped descriptor: views, tiles, views * N
+    // clamped descriptor: views, tiles, views * N
+    uint32_t* bctl = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(ws) + need.bytes);
     uint32_t* n_entries = bctl + 2;
     const ts::Cfg g = to_cfg(cfg);
 

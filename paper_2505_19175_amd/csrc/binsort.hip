@@ -452,11 +452,9 @@ void launch_fill_u32(uint32_t* p, int64_t n, uint32_t x, hipStream_t stream)
 // Tiles by decreasing list length (counting sort on the length, lengths of
 // 2047 and more share the first bucket; order inside a bucket is arbitrary).
 // Rasterizing the longest tiles first keeps them out of the tail of the
-// launch.  One workgroup; ctl (optional) holds the number of tiles.
+// launch.
 constexpr int kLenBuckets = 2048;
 
-// n_long (optional) receives the number of tiles longer than kWaveSortMax:
-// they lead the order, since kWaveSortMax < kLenBuckets - 1.
 constexpr int kWaveMax = 1024;   // longest list one wave's register network holds
 // Longer lists get a whole workgroup (four quarter sorts and a merge): the
 // quarters' shorter compare-exchange chains finish sooner than one wave's.
@@ -469,7 +467,9 @@ constexpr int kOrderThreads = 1024;
 constexpr int kHugeLen = 4 * kWaveMax;   // longest list one workgroup sorts in LDS
 
 // The order of tiles 0 .. n-1 by one workgroup of kOrderThreads; len_of(t)
-// gives a tile's list length.
+// gives a tile's list length.  n_long and n_huge (optional) receive the number
+// of tiles longer than kWaveSortMax (they lead the order, since kWaveSortMax <
+// kLenBuckets - 1) and than kHugeLen.
 struct OrderSmem {
     uint32_t h[kLenBuckets];
     uint32_t w[kOrderThreads / 64];
@@ -942,15 +942,14 @@ __device__ __forceinline__ void put(uint32_t* cursor, uint32_t id, uint32_t capa
 // One workgroup bins everything (N <= kOneEntries entries of one view, T <=
 // kGroupTiles).
 __global__ __launch_bounds__(kGroupThreads) void k_bin_one(
-    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T, const uint32_t* __restrict__ d_tiles,
+    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, int N, int tiles_x, int T,
     GroupOut o, uint32_t* __restrict__ vals)
 {
     extern __shared__ uint32_t s_t[];   // [T] counts, then starts, then cursors
     __shared__ OrderSmem sm;
     __shared__ uint32_t s_tmp[kGroupThreads / 64], s_tmp2[kGroupThreads / 64];
     const int tid = threadIdx.x;
-    const int64_t N = tg.N;
-    const ViewTiles vt{0u, tg.tiles_x};
+    const ViewTiles vt{0u, tiles_x};
     constexpr int kRounds = kOneEntries / kGroupThreads;
     Run<1> u[kRounds];
 #pragma unroll
@@ -972,7 +971,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_bin_one(
         write_totals(M, o);
         *o.d_Nv = vis;
     }
-    write_ranges(s_t, T, d_tiles ? (int)min(*d_tiles, (uint32_t)T) : T, M, o, sm);
+    write_ranges(s_t, T, T, M, o, sm);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kRounds; ++k)
@@ -999,8 +998,9 @@ __device__ __forceinline__ uint32_t bump(uint32_t* s, uint32_t t)
 // the T budgeted) are counted, and the grid clears all ranges.
 template <int R, bool WIDE>
 __global__ __launch_bounds__(kGroupThreads) void k_group_count(
-    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T, const uint32_t* __restrict__ d_tiles,
-    int G, uint32_t* __restrict__ hist, uint32_t* __restrict__ grp, uint32_t* __restrict__ ranges)
+    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T,
+    const uint32_t* __restrict__ d_tiles, int G, uint32_t* __restrict__ hist,
+    uint32_t* __restrict__ grp, uint32_t* __restrict__ ranges)
 {
     extern __shared__ uint32_t s_h[];   // [T] counters
     __shared__ uint32_t s_tmp[kGroupThreads / 64];
@@ -1097,9 +1097,10 @@ __device__ __forceinline__ uint32_t sum_groups(const uint32_t* __restrict__ grp,
 // tile totals in tot.
 template <int R, bool FOLD>
 __global__ __launch_bounds__(kGroupThreads) void k_group_place(
-    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T, const uint32_t* __restrict__ d_tiles,
-    int G, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ tot,
-    const uint32_t* __restrict__ grp, GroupOut o, uint32_t* __restrict__ vals)
+    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T,
+    const uint32_t* __restrict__ d_tiles, int G, const uint32_t* __restrict__ hist,
+    const uint32_t* __restrict__ tot, const uint32_t* __restrict__ grp, GroupOut o,
+    uint32_t* __restrict__ vals)
 {
     extern __shared__ uint32_t s_t[];   // [T] totals, then starts, then cursors
     __shared__ OrderSmem sm;
@@ -1195,9 +1196,9 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_ranges_wide(
 // group's instances, a window of tiles at a time.
 template <int R>
 __global__ __launch_bounds__(kGroupThreads) void k_group_place_wide(
-    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T, const uint32_t* __restrict__ d_tiles,
-    int G, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ start, GroupOut o,
-    uint32_t* __restrict__ vals)
+    const uint32_t* __restrict__ ntiles, const uint2* __restrict__ rect, TileGrid tg, int T,
+    const uint32_t* __restrict__ d_tiles, int G, const uint32_t* __restrict__ hist,
+    const uint32_t* __restrict__ start, GroupOut o, uint32_t* __restrict__ vals)
 {
     __shared__ uint32_t s_t[kWideTiles];   // cursors (64 KB)
     static_assert(sizeof(OrderSmem) <= sizeof(s_t), "the order workgroup's tables");
@@ -2069,9 +2070,9 @@ hipError_t run_bin_sort(const uint32_t* ntiles, const float* depth, const int16_
             hipLaunchKernelGGL(k_group_place_wide<8>, dim3((unsigned)G + 1), blk, 0, stream,
                                ntiles, r4, tg, num_tiles, d_tiles, G,
                                (const uint32_t*)ws.hist, (const uint32_t*)ws.cst, go, out.vals);
-        } else if (N <= kOneEntries && !views) {
-            hipLaunchKernelGGL(k_bin_one, dim3(1), blk, lds, stream, ntiles, r4, tg,
-                               num_tiles, d_tiles, go, out.vals);
+        } else if (N <= kOneEntries && !views && !d_n && !d_tiles) {
+            hipLaunchKernelGGL(k_bin_one, dim3(1), blk, lds, stream, ntiles, r4, (int)N, tiles_x,
+                               num_tiles, go, out.vals);
         } else {
             auto place = [&](auto kern) {
                 hipLaunchKernelGGL(kern, dim3((unsigned)G + 1), blk, lds, stream, ntiles, r4,

@@ -207,8 +207,9 @@ __global__ __launch_bounds__(kDensBlock) void k_sum_counts(const uint32_t* __res
 //
 // A workgroup takes a chunk of triangles: it adds the counts of the chunks
 // before it (and of all, for the capacity test: nothing is written when the
-// soup does not fit; SPANS: by their sums over spans of chunks), lists its selected triangles in LDS, and writes the
-// children of consecutive ranks, which are contiguous, element by element.
+// soup does not fit; SPANS: by their sums over spans of chunks), lists its
+// selected triangles in LDS, and writes the children of consecutive ranks, which
+// are contiguous, element by element.
 // Bound by HBM (the SH rows: 192 bytes read and 576 written per selected
 // triangle): with a wave copying one selected row at a time, each row's load
 // exposed its latency.  The SH rows and the rest go to different workgroups

@@ -100,7 +100,7 @@ struct FwdStage : StageExtra<WIN, kBatch> {
 // fewest tiles of an image that has wide entries summed
 constexpr int kWideImage = 1024, kWideImageSigmoid = 800;
 constexpr int kWideSlots = 10;           // what 25 LDS allocation units leave room for
-constexpr int kWideBlocks = 8;           // blocks of the tile that make an entry wide (4, 6: +1 us at 3M)
+constexpr int kWideBlocks = 8;           // blocks that make an entry wide (4, 6: +1 us at 3M)
 constexpr uint32_t kWideTri = 0xffffff00u;   // above any triangle: a slot, not a triangle
 
 // The backward's LDS.  The gradients of an entry take one line of global atomics
@@ -154,15 +154,6 @@ union RecView {
     TriRecord r;
 };
 
-// Copy record `tri` into LDS slot threadIdx.x and return the mask of the
-// tile's sixteen 4x4 blocks that may hold a composited pixel of it: the
-// tight box touches the block, and for every edge k the largest u_k over the
-// block's pixel centres (at one corner, u_k being affine) reaches ut, the
-// lower bound of u over pixels that composite.  The box and the three edge
-// tests are the separating axes of the tight region (a triangle) and the
-// block's square of pixel centres.  The slack covers the rounding of this
-// evaluation and of the per-pixel one, so no pixel that composites is lost.
-//
 // The staged copy holds C_k relative to the tile's corner pixel (tx0, ty0)
 // instead of the record's anchor, so a lane evaluates u_k = A_k dx + B_k dy +
 // C_k with its own fixed offset in the tile (no per-step conversion).  The
@@ -180,7 +171,7 @@ __device__ __forceinline__ void write_stage(Stage& S, RecView& u, int tx0, int t
     if constexpr (Stage::kLse) S.ps[threadIdx.x] = u.r.phis;
 }
 
-template <bool ZA = false, class Stage>
+template <class Stage>
 __device__ __forceinline__ void stage_copy(Stage& S, const TriRecord* __restrict__ rec,
                                            uint32_t tri, int tx0, int ty0)
 {
@@ -189,11 +180,19 @@ __device__ __forceinline__ void stage_copy(Stage& S, const TriRecord* __restrict
     constexpr int nc = Stage::kLse ? 8 : 7;   // phis sits in chunk 7
 #pragma unroll
     for (int c = 0; c < nc; ++c) u.q[c] = src[c];
-    write_stage<ZA>(S, u, tx0, ty0);
-    if constexpr (!ZA) S.zt[threadIdx.x] = make_uint2(__float_as_uint(u.r.z), tri);
+    write_stage<false>(S, u, tx0, ty0);
+    S.zt[threadIdx.x] = make_uint2(__float_as_uint(u.r.z), tri);
 }
 
-template <bool ZA = false, class Stage>
+// Copy record `tri` into LDS slot threadIdx.x and return the mask of the
+// tile's sixteen 4x4 blocks that may hold a composited pixel of it: the
+// tight box touches the block, and for every edge k the largest u_k over the
+// block's pixel centres (at one corner, u_k being affine) reaches ut, the
+// lower bound of u over pixels that composite.  The box and the three edge
+// tests are the separating axes of the tight region (a triangle) and the
+// block's square of pixel centres.  The slack covers the rounding of this
+// evaluation and of the per-pixel one, so no pixel that composites is lost.
+template <class Stage>
 __device__ __forceinline__ uint32_t stage_rec(Stage& S, const TriRecord* __restrict__ rec,
                                               uint32_t tri, int tx0, int ty0)
 {
@@ -201,8 +200,8 @@ __device__ __forceinline__ uint32_t stage_rec(Stage& S, const TriRecord* __restr
     RecView u;
 #pragma unroll
     for (int c = 0; c < 8; ++c) u.q[c] = src[c];
-    write_stage<ZA>(S, u, tx0, ty0);
-    if constexpr (!ZA) S.zt[threadIdx.x] = make_uint2(__float_as_uint(u.r.z), tri);
+    write_stage<false>(S, u, tx0, ty0);
+    S.zt[threadIdx.x] = make_uint2(__float_as_uint(u.r.z), tri);
     uint32_t cx = 0, cy = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1190,7 +1189,8 @@ void launch_raster_backward(const void* rec, const uint32_t* vals, const uint32_
         num_tiles >= (cfg.window == TS_WINDOW_SIGMOID ? kWideImageSigmoid : kWideImage);
     switch (cfg.window) {
     case TS_WINDOW_SIGMOID:
-        wide ? go(k_raster_bwd<TS_WINDOW_SIGMOID, false, true>) : go(k_raster_bwd<TS_WINDOW_SIGMOID>);
+        wide ? go(k_raster_bwd<TS_WINDOW_SIGMOID, false, true>)
+             : go(k_raster_bwd<TS_WINDOW_SIGMOID>);
         break;
     case TS_WINDOW_LSE:
         wide ? go(k_raster_bwd<TS_WINDOW_LSE, false, true>) : go(k_raster_bwd<TS_WINDOW_LSE>);
