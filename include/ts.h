@@ -134,7 +134,8 @@ typedef struct ts_bins {
     uint64_t* keys;     /* [capacity] (tile << 32) | depth bits, sorted; may be NULL */
     uint32_t* vals;     /* [capacity] triangle index of each instance, sorted */
     uint32_t* ranges;   /* [tiles][2] [start, end) of each tile in vals; (0,0) if empty */
-    uint32_t* d_count;  /* [4] device counters: [0] instances M, [1] visible N_v,
+    uint32_t* d_count;  /* [4] device counters: [0] instances M (2^32 - 1 stands for
+                           more, too, which no list holds), [1] visible N_v,
                            [2] overflow flag (M > capacity), [3] tiles holding more
                            than 4096 instances */
     uint64_t capacity;  /* entries available in keys / vals */

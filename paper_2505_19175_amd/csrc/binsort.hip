@@ -109,6 +109,19 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t& t
     return wbase + inc - x;
 }
 
+// Sum of one value per thread, which 32 bits need not hold.
+__device__ __forceinline__ uint64_t block_sum64(uint64_t x, unsigned long long* s_tmp)
+{
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) x += __shfl_xor((unsigned long long)x, d, 64);
+    if ((threadIdx.x & 63) == 0) s_tmp[threadIdx.x >> 6] = x;
+    __syncthreads();
+    x = 0;
+#pragma unroll
+    for (int j = 0; j < kBlock / 64; ++j) x += s_tmp[j];
+    return x;
+}
+
 // ---------------------------------------------------------------------------
 // 1. tile counts in index order
 // ---------------------------------------------------------------------------
@@ -163,8 +176,8 @@ __global__ __launch_bounds__(256) void k_count(const uint32_t* __restrict__ ntil
 // thread's kItems entries, and its tile from the entry's tile rectangle.
 // The block's first output slot is the sum of the counts of the blocks before
 // it (k_count's per-block totals, summed here by each block: no separate scan
-// launch); the last block also writes the totals: M, min(M, capacity) for the
-// sort, the overflow flag and N_v.
+// launch); the last block also writes the totals: M (saturated), min(M,
+// capacity) for the sort, the overflow flag and N_v.
 __global__ __launch_bounds__(256) void k_emit(const uint32_t* __restrict__ ntiles,
                                               const short4* __restrict__ rect, int64_t N_host,
                                               const uint32_t* __restrict__ d_n,
@@ -178,6 +191,7 @@ __global__ __launch_bounds__(256) void k_emit(const uint32_t* __restrict__ ntile
                                               uint32_t* __restrict__ d_Nv)
 {
     __shared__ uint32_t s_tmp[4];
+    __shared__ unsigned long long s_tmp64[4];
     __shared__ uint32_t s_pre[kBlock];         // instances before each thread's entries
     __shared__ uint32_t s_cnt[kChunk];         // tiles of entry tid * kItems + r at r * kBlock + tid
     const int64_t N = d_n ? (int64_t)*d_n : N_host;
@@ -192,7 +206,8 @@ __global__ __launch_bounds__(256) void k_emit(const uint32_t* __restrict__ ntile
     const int tid = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * kChunk;
     const bool last_block = (int64_t)blockIdx.x == nb - 1;
-    uint32_t before = 0, vis = 0;
+    uint64_t before = 0;
+    uint32_t vis = 0;
     for (int64_t b = tid; b < (int64_t)blockIdx.x; b += kBlock) before += blk[b];
     if (last_block)
         for (int64_t b = tid; b < nb; b += kBlock) vis += blk_vis[b];
@@ -218,21 +233,20 @@ __global__ __launch_bounds__(256) void k_emit(const uint32_t* __restrict__ ntile
             c += n;
         }
     }
-    uint32_t tot, out0_32, vis_tot;
+    uint32_t tot, vis_tot;
     s_pre[tid] = block_exclusive_scan(c, tot, s_tmp);
-    block_exclusive_scan(before, out0_32, s_tmp);
+    const uint64_t out0 = block_sum64(before, s_tmp64);
     if (last_block) {
         block_exclusive_scan(vis, vis_tot, s_tmp);
         if (tid == 0) {
-            const uint64_t M = (uint64_t)out0_32 + tot;
-            *d_M = (uint32_t)M;
+            const uint64_t M = out0 + tot;
+            *d_M = (uint32_t)min(M, (uint64_t)0xffffffffu);
             *d_sortn = M > capacity ? (uint32_t)capacity : (uint32_t)M;
             *d_ovf = M > capacity ? 1u : 0u;
             *d_Nv = vis_tot;
         }
     }
     __syncthreads();
-    const uint64_t out0 = (uint64_t)out0_32;
     for (uint32_t q = tid; q < tot; q += kBlock) {
         if (out0 + q >= capacity) break;
         int t = 0;   // last thread whose first instance is at or before q
@@ -608,6 +622,8 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tfi
 //   3M, 3600 tiles              52.2 -> 47 us
 //   batch of 1 view of 1M, 920 tiles      57 -> 25 us
 //   batch of 4 views of 1M, 13600 tiles   92 -> 75 us
+// A batch's soup that its groups' 16-bit counters cannot hold (wide_fits: with
+// room for eight views, more than 2.1M triangles) keeps the radix chain.
 constexpr int kGroupThreads = 1024;
 constexpr int kMaxGroups = 256;
 constexpr int kGroupEntries = 1024;   // fewest entries per group
@@ -2114,7 +2130,7 @@ hipError_t run_bin_sort(const uint32_t* ntiles, const float* depth, const int16_
         if (err != hipSuccess) return err;
         err = hipStreamSynchronize(stream);
         if (err != hipSuccess) return err;
-        if ((uint64_t)h_count[0] > out.capacity) {
+        if ((uint64_t)h_count[0] > out.capacity || h_count[0] == 0xffffffffu) {
             // ranges are all empty here; keep the order valid for any raster
             // launched before the caller grows the list
             *overflow = true;

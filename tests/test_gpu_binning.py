@@ -394,3 +394,31 @@ def test_view_of_more_tiles_than_the_groups_count(mul):
         assert torch.equal(st.vals[:st.M], ref.vals[:st.M]) and torch.equal(st.ranges, ref.ranges)
         for a, b in ((out.rgb, want.rgb), (out.alpha, want.alpha), (out.depth, want.depth)):
             assert torch.equal(a, b)
+
+
+# The radix chain past 2^32 instances: a 4K view (32400 tiles), and a state that
+# sorts huge tiles segment-wise.
+@pytest.mark.parametrize("n,W,H,segmented", [(140_000, 3840, 2160, False),
+                                             (540_000, 1920, 1080, True)])
+def test_radix_chain_past_32_bits(n, W, H, segmented):
+    scene = scene_to_device(_covering(n), DEV)
+    cap = 100_000
+    st, ras = ViewState(n, W, H, cap), Rasterizer(synth.Config(sh_degree=0))
+    if segmented:
+        Rasterizer._seen_huge(st, 1)
+    cam = synth.identity_camera(W, H)
+    with pytest.raises(B.TSError) as e:
+        ras.forward(st, scene, cam, sync=True)
+    assert e.value.code == B.TS_ECAPACITY and st.capacity == cap
+    out = ras.forward(st, scene, cam, sync=False)
+    torch.cuda.synchronize()
+    d = st.d_count.cpu().numpy().view(np.uint32)
+    assert d[0] == 0xffffffff and d[1] == n and d[2] == 1
+    r = st.ranges.cpu().numpy()
+    _disjoint_runs(r, cap)
+    vals, depth = st.vals.cpu().numpy(), st.depth_key.cpu().numpy()
+    assert (vals >= 0).all() and (vals < n).all()
+    for t in np.flatnonzero(r[:, 1] > r[:, 0])[::500]:
+        run = vals[r[t, 0]:r[t, 1]]
+        assert (np.lexsort((run, depth[run])) == np.arange(len(run))).all()
+    assert bool(torch.isfinite(out.rgb).all())
