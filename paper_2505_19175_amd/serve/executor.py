@@ -160,7 +160,7 @@ class BatchedExecutor:
         done = self.clock()
         s.stream.synchronize()            # the 16-byte count copy queued after the event
         c = s.count_host.numpy()
-        res = BatchResult(done=done, instances=int(c[0]), overflow=bool(c[2]))
+        res = BatchResult(done=done, instances=int(c[0]) & 0xffffffff, overflow=bool(c[2]))
         s.batch = None
         return res
 

@@ -212,7 +212,7 @@ def test_batch_of_more_instances_than_32_bits():
     ex.submit(0, batch)
     while (res := ex.poll(0)) is None:
         pass
-    assert res.overflow and ex._slots[0].count_host.numpy().view(np.uint32)[0] == 0xffffffff
+    assert res.overflow and res.instances == 0xffffffff
     _disjoint_runs(ex._slots[0].ranges.cpu().numpy(), cap)
     for rgb, alpha, depth in ex.outputs(0, batch):
         assert all(bool(torch.isfinite(x).all()) for x in (rgb, alpha, depth))
