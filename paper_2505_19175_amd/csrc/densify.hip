@@ -18,12 +18,13 @@ constexpr int kPickChunk = 4 * kDensBlock;   // triangles per workgroup of the s
 // after another on an idle chip).
 constexpr int kMany = 8, kFew = 2;
 constexpr int64_t kFewTriangles = 1 << 18;
-// From these sizes on, the sums that every workgroup would repeat get a launch of
+// From this size on, the sums that every workgroup would repeat get a launch of
 // their own, since both the workgroups and the sums grow with the soup.  Selection,
-// repeated / own launch: 2M 12.4 / 13.7 us, 4M 20.3 / 20.2, 8M 37.8 / 31.9, 100M
+// repeated / own launch: 3M 15.2 / 16.5 us, 4M 20.3 / 20.2, 8M 37.8 / 31.9, 100M
 // 1260 / 292.  Subdivision (sums over spans of the chunk counts): 1M 34.6 / 37.0,
-// 2M 53.9 / 54.8, 3M 77.3 / 73.1, 30M 934 / 879, 200M 10037 / 5722.
-constexpr int64_t kManyWeights = 4 << 20, kManyCounts = 2 << 20;
+// 3M 77.3 / 73.1 (84.2 / 85.7 in the training benchmark), 4M 112 / 104, 30M 934 /
+// 879, 200M 10037 / 5722.
+constexpr int64_t kManyTriangles = 4 << 20;
 
 __device__ __forceinline__ double dens_weight(float o_or_sigma, int mode)
 {
@@ -367,7 +368,7 @@ void launch_densify_select(const float* o, const float* sigma, int64_t N, int mo
     const float* x = mode == TS_DENSIFY_OPACITY ? o : sigma;
     hipLaunchKernelGGL(k_weight_partial, dim3((unsigned)nw), dim3(kDensBlock), 0, stream, x, N,
                        mode, partial);
-    const bool total = N > kManyWeights;
+    const bool total = N > kManyTriangles;
     if (total)
         hipLaunchKernelGGL(k_weight_total, dim3(1), dim3(kDensBlock), 0, stream,
                            (const double*)partial, nw, partial + nw);
@@ -399,7 +400,7 @@ void launch_densify_subdivide(float* v, float* o, float* sigma, float* sh, int n
     const std::integral_constant<int, kFew> few;
     const std::integral_constant<int, kMany> many;
     if (N <= kFewTriangles) go(few, std::false_type{});
-    else if (N <= kManyCounts) go(many, std::false_type{});
+    else if (N <= kManyTriangles) go(many, std::false_type{});
     else go(many, std::true_type{});
 }
 

@@ -173,7 +173,7 @@ def test_select_from_unaligned_arrays():
                                                         u[1:]))
 
 
-# Around the sizes from which the sums get launches of their own: the same
+# Around the size from which the sums get launches of their own: the same
 # decisions and children on both sides.
 @pytest.mark.parametrize("N", [1 << 22, (1 << 22) + 1, 9_000_001])
 def test_select_of_large_soups(N):
@@ -182,8 +182,8 @@ def test_select_of_large_soups(N):
     assert _check_select(o, o, B.TS_DENSIFY_OPACITY, 0.1 * N, u) > 0
 
 
-@pytest.mark.parametrize("N,share", [(1 << 21, 0.1), ((1 << 21) + 1, 0.1), ((1 << 21) + 1, 1.0),
-                                     (1025 * 2048 + 7, 0.0), (5_000_003, 0.3)])
+@pytest.mark.parametrize("N,share", [(1 << 22, 0.1), ((1 << 22) + 1, 0.1), ((1 << 22) + 2049, 0.0),
+                                     (2305 * 2048 + 7, 0.01), (5_000_003, 0.3)])
 def test_subdivide_of_large_soups(N, share):
     v, o, s, sh = _soup(35, N, 0)
     sel = np.random.default_rng(36).random(N) < share
