@@ -945,12 +945,13 @@ static uint32_t list_capacity(uint64_t capacity)
 }
 
 // Puts instance id of a tile at the tile's cursor, unless that is past the
-// capacity (as the clamped ranges say).  `full`: the list does not hold all
+// capacity (as the clamped ranges say).  FULL: the list does not hold all
 // instances, and a cursor that has reached the capacity stays there.
-__device__ __forceinline__ void put(uint32_t* cursor, uint32_t id, uint32_t capacity, bool full,
+template <bool FULL>
+__device__ __forceinline__ void put(uint32_t* cursor, uint32_t id, uint32_t capacity,
                                     uint32_t* __restrict__ vals)
 {
-    if (full && *reinterpret_cast<volatile uint32_t*>(cursor) >= capacity) return;
+    if (FULL && *reinterpret_cast<volatile uint32_t*>(cursor) >= capacity) return;
     const uint32_t p = atomicAdd(cursor, 1u);
     if (p < capacity) vals[p] = id;
 }
@@ -992,7 +993,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_bin_one(
 #pragma unroll
     for (int k = 0; k < kRounds; ++k)
         for_run_tiles<1>(k * kGroupThreads + tid, u[k], vt, [&](uint32_t t, uint32_t id) {
-            if (t < (uint32_t)T) put(&s_t[t], id, o.capacity, false, vals);   // far below 2^32
+            if (t < (uint32_t)T) put<false>(&s_t[t], id, o.capacity, vals);   // far below 2^32
         });
 }
 
@@ -1161,9 +1162,14 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place(
         if (t < T) s_t[t] = first_slot(s_t[t], before[k], o.capacity);
     }
     __syncthreads();
-    const bool full = M > o.capacity;
+    if (M > o.capacity) {   // a walk of its own: a test per instance cost 10% at 6.4M of them
+        for_group_tiles<R>(G, g, ntiles, rect, tg, [&](uint32_t t, uint32_t id) {
+            if (t < (uint32_t)T) put<true>(&s_t[t], id, o.capacity, vals);
+        });
+        return;
+    }
     for_group_tiles<R>(G, g, ntiles, rect, tg, [&](uint32_t t, uint32_t id) {
-        if (t < (uint32_t)T) put(&s_t[t], id, o.capacity, full, vals);
+        if (t < (uint32_t)T) put<false>(&s_t[t], id, o.capacity, vals);
     });
 }
 
@@ -1238,10 +1244,17 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_place_wide(
         for (int t = tid; t < m; t += kGroupThreads)
             s_t[t] = first_slot(start[w0 + t], row[w0 + t], o.capacity);
         __syncthreads();
-        for_group_tiles<R>(G, g, ntiles, rect, tg, [&](uint32_t t, uint32_t id) {
-            const uint32_t tw = t - (uint32_t)w0;
-            if (tw < (uint32_t)m) put(&s_t[tw], id, o.capacity, full, vals);
-        });
+        if (full) {
+            for_group_tiles<R>(G, g, ntiles, rect, tg, [&](uint32_t t, uint32_t id) {
+                const uint32_t tw = t - (uint32_t)w0;
+                if (tw < (uint32_t)m) put<true>(&s_t[tw], id, o.capacity, vals);
+            });
+        } else {
+            for_group_tiles<R>(G, g, ntiles, rect, tg, [&](uint32_t t, uint32_t id) {
+                const uint32_t tw = t - (uint32_t)w0;
+                if (tw < (uint32_t)m) put<false>(&s_t[tw], id, o.capacity, vals);
+            });
+        }
     }
 }
 
