@@ -40,7 +40,7 @@ TRAFFIC = {
     "project_bwd": {"files": ["paper_2505_19175_amd/csrc/backproject.hip",
                               "paper_2505_19175_amd/csrc/geometry.h",
                               "paper_2505_19175_amd/csrc/ts_device.h"],
-                    "src": "cd6fa70cd90c6bd24183b5b358c63bae077cb5e234b05634044a53f10cc690c8",
+                    "src": "e8f8b25a328bd59b045ae293fbe1f600f2fc5c1b0cbc614ecef38ee84df20314",
                     "fetch_kib": 1.615e5, "write_kib": 7.807e5,
                     "fetch_scale": 2.0, "write_scale": 1.0},
     "project": {"files": ["paper_2505_19175_amd/csrc/project.hip",
